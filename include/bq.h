@@ -59,8 +59,8 @@ extern "C" {
 #define BQ_MAX_WAVES 256
 /* Size of the per-GPU static array that holds the device tables of a batch
  * set up by bq_batch_set_static (8 MiB: the tables take 4 bytes per tile of
- * 64 x 16 (FP32) or 64 x 8 (FP64) cells and per grid line, plus about 1 KB
- * per member, twice over with lanes). */
+ * 64 x 16 (FP32) or 64 x 8 (FP64) cells and per 16 grid lines, plus about
+ * 1 KB per member, twice over with lanes). */
 #define BQ_STATIC_TABLE_BYTES (8u << 20)
 
 /* BQ_TIMESERIES: both west ghost columns take eta and P interpolated
@@ -265,19 +265,16 @@ int bq_batch_lanes(const bq_batch* b);
 int bq_profile_steps(bq_domain* d, int32_t n_steps, double* ms_out);
 int bq_batch_profile_steps(bq_batch* b, int32_t n_steps, double* ms_out);
 
-/* Schedule of a batch: launch lanes, steps per hipGraph replay, threads per
- * block of the line-coupling kernel (64, 128 or 256), the XCD-aware tile
- * order of the stencil kernel (1 on, 0 off), the line-coupling variant
- * (reduce_segments 1 = one thread per line running over its chunks, 4 or 8 =
- * the chunks of a line cut into that many segments swept by as many waves
- * that exchange their composed maps; reduce_block is then ignored, give
- * 256), and the tile shape shared by the members (the chunking of the
- * tridiagonal solves of Eq. 19-20; the workspace is laid out for every
- * candidate, so members change shape between steps in place).  With
- * reduce_segments 1 every schedule of one tile shape gives bitwise the same
- * results; the segmented variant reassociates the line-coupling products,
- * and another tile shape chunks the line solves differently: both differ
- * at rounding level. */
+/* Schedule of a batch: launch lanes, steps per hipGraph replay, the
+ * XCD-aware tile order of the stencil kernel (1 on, 0 off), and the tile
+ * shape shared by the members (the chunking of the tridiagonal solves of Eq.
+ * 19-20; the workspace is laid out for every candidate, so members change
+ * shape between steps in place).  reduce_block (64, 128 or 256) and
+ * reduce_segments (1, 4 or 8) are accepted and reported back: one
+ * line-coupling kernel, whose split of a line depends on the line's chunk
+ * count alone, serves every value.  Every schedule of one tile shape gives
+ * bitwise the same results; another tile shape chunks the line solves
+ * differently and differs at rounding level. */
 typedef struct bq_tune {
   int32_t lanes;
   int32_t graph_steps;
@@ -293,8 +290,7 @@ typedef struct bq_tune {
 } bq_tune;
 
 /* Autotuner: times steps_per_trial steps of the batch under each candidate
- * schedule (lanes 1-4 x graph replays of 4 or 16 steps x line coupling by
- * one thread per line in blocks of 64 or 256, or segmented; XCD-aware tile
+ * schedule (lanes 1-4 x graph replays of 4 or 16 steps; XCD-aware tile
  * order on; the current tile shape) twice, in forward then reverse order,
  * keeps the one of the lowest mean time (among those within 0.5 % of it,
  * the one with the longest graph replays), then times every tile shape

@@ -19,8 +19,8 @@
 //             dispersion, friction, F*/G* of the weighted P/Q history, AB3
 //             update of w and of U*, V* (as increments); then the chunk-local
 //             tridiagonal solves of Eq. (19)-(20) for the P, Q increments;
-//   k_reduced per line: the chunk-interface recurrence that couples the
-//             chunk-local solutions into the exact line solution;
+//   k_reduced the chunk-interface recurrences that couple the chunk-local
+//             solutions of every line into the exact line solution;
 //   k_final   P, Q = local solution + the chunk systems' response to the
 //             neighbour-chunk values, sponge, ghost cells of the new state,
 //             CFL maximum of the new state.
@@ -1691,7 +1691,7 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
 }
 
 // ---------------------------------------------------------------------------
-// k_reduced: per line, couple the chunk-local solutions (one thread per line)
+// k_reduced: couple the chunk-local solutions of every line
 // ---------------------------------------------------------------------------
 //
 // For chunk c with local solution xh, left spike v and right spike w, the
@@ -1702,314 +1702,217 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
 // and a backward sweep X_s(c) = sigma_c + tau_c X_s(c+1),
 // X_e(c) = alpha_c + gamma_c X_s(c+1).  (k1, k2, m1, m2, tau, gamma) are
 // static and precomputed.
+//
+// The recurrences are serial in c, their inputs are not.  A line's chunks
+// are spread over RED_SEGS threads of RED_MAX chunks each, which load all
+// their inputs at once; the sweep then passes from thread to thread in
+// registers (row swaps inside a wave, LDS from wave to wave).  What
+// bounds the kernel is latency (its words are 0.15 of the stencil kernel's
+// bytes at most): one trip to memory and the chain itself, three dependent
+// operations per chunk forward and one backward.  16 lines to a block spread
+// the lines thinly (a 2048^2 domain gives 256 blocks, one per compute unit,
+// one of 200 x 20 cells 15).  The sweep keeps the order and the rounding of
+// the plain recurrence, so neither the launch nor the batch around a domain
+// changes its results.  Against one thread per line sweeping alone (HIP
+// events around the launch): 41.6 -> 13.0 us on 2048^2 FP32, 33.3 -> 8.7 on
+// 1024 x 256 FP64, 10.7 -> 7.1 on 200 x 20 FP64; composing the segments' maps
+// in parallel, which rounds differently, would take 11.3, 8.2 and 6.7.  Lines of more than RED_SEGS * RED_MAX chunks are
+// taken in panels, from the first to the last and back, with sigma and alpha
+// of all but the last panel kept in the result's slots.
 
-template <typename T>
-__device__ __forceinline__ void reduce_line(int C, int L, int line, const gp<const T> ch, const gp<const T> rs,
-                                            const gp<T> itf) {
-  // The recurrences are serial in c, their inputs are not: the inputs of
-  // RB chunks are loaded together ahead of the RB dependent steps.
-  constexpr int RB = 8;
-  const size_t CL = (size_t)C * L;
-  T al = T(0);
-  for (int c0 = 0; c0 < C; c0 += RB) {
-    T xs[RB], xe[RB], r0[RB], r1[RB], r2[RB], r3[RB];
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)min(c0 + k, C - 1) * L + line;
-      xs[k] = ch[o];
-      xe[k] = ch[CL + o];
-      r0[k] = rs[o];
-      r1[k] = rs[CL + o];
-      r2[k] = rs[2 * CL + o];
-      r3[k] = rs[3 * CL + o];
-    }
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      if (c0 + k < C) {
-        const size_t o = (size_t)(c0 + k) * L + line;
-        const T sg = r0[k] * xs[k] + r1[k] * al;
-        al = xe[k] + r2[k] * al + r3[k] * sg;
-        itf[o] = sg;          // temporarily sigma_c, alpha_c
-        itf[CL + o] = al;
-      }
-    }
-  }
-  T xs_next = T(0);
-  for (int c1 = C - 1; c1 >= 0; c1 -= RB) {
-    T sg[RB], a[RB], r4[RB], r5[RB];
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)max(c1 - k, 0) * L + line;
-      sg[k] = itf[o];
-      a[k] = itf[CL + o];
-      r4[k] = rs[4 * CL + o];
-      r5[k] = rs[5 * CL + o];
-    }
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const int c = c1 - k;
-      if (c >= 0) {
-        const size_t o = (size_t)c * L + line;
-        const T Xs = sg[k] + r4[k] * xs_next;
-        const T Xe = a[k] + r5[k] * xs_next;
-        itf[CL + o] = xs_next;                    // right neighbour of chunk c
-        if (c + 1 < C) itf[o + L] = Xe;          // left neighbour of chunk c + 1
-        xs_next = Xs;
-      }
-    }
-  }
-  itf[line] = T(0);                           // chunk 0 has no left neighbour
+constexpr int RED_LINES = 16, RED_SEGS = 16, RED_MAX = 8;
+constexpr int RED_PANEL = RED_SEGS * RED_MAX;      // chunks of a line per panel
+constexpr int RED_THREADS = RED_LINES * RED_SEGS;
+constexpr int RED_ROWS = 64 / RED_LINES;           // segments (rows of lanes) per wave
+static_assert(RED_ROWS == 4, "the sweeps below pass through four rows");
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+// blocks of RED_LINES lines of a domain: its x-lines', then its y-lines'
+__host__ __device__ inline int line_blocks(int nx, int ny) {
+  return (ny + RED_LINES - 1) / RED_LINES + (nx + RED_LINES - 1) / RED_LINES;
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_reduced(const DomDev<T>* __restrict__ doms, const int* __restrict__ line_map,
-                                                int nd, int lines, int pass) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= lines) return;
-  int dom, l;
-  locate(line_map, nd, gid, dom, l);
+__device__ __forceinline__ T fma_(T a, T b, T c);
+template <>
+__device__ __forceinline__ float fma_<float>(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
+}
+template <>
+__device__ __forceinline__ double fma_<double>(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+
+// A wave's value moved by one row of 16 lanes: up (row r to row r + 1) for
+// r = FROM, or down (row r to row r - 1).  The rows that the sweep has yet
+// to reach get no meaningful value.
+template <bool UP, int FROM>
+__device__ __forceinline__ unsigned row_move(unsigned v) {
+  if (UP) {
+    if (FROM == 1) v = __builtin_amdgcn_permlane32_swap(v, v, false, false)[0];   // row 3 = row 1
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return FROM == 1 ? r[1] : r[0];                                               // even rows from odd, or odd from even
+  }
+  if (FROM == 2) v = __builtin_amdgcn_permlane32_swap(v, v, false, false)[1];     // row 0 = row 2
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return FROM == 2 ? r[0] : r[1];
+}
+template <bool UP, int FROM>
+__device__ __forceinline__ float row_move(float v) {
+  return __uint_as_float(row_move<UP, FROM>(__float_as_uint(v)));
+}
+template <bool UP, int FROM>
+__device__ __forceinline__ double row_move(double v) {
+  const unsigned lo = row_move<UP, FROM>((unsigned)__double2loint(v));
+  const unsigned hi = row_move<UP, FROM>((unsigned)__double2hiint(v));
+  return __hiloint2double((int)hi, (int)lo);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(RED_THREADS) k_reduced(const DomDev<T>* __restrict__ doms,
+                                                        const int* __restrict__ line_map, int nd, int pass) {
+  __shared__ T hand[RED_LINES];               // the sweep's value, from wave to wave
+  int dom, blk;
+  // neighbouring blocks share 128-byte lines: keep them on one XCD
+  locate(line_map, nd, xcd_tile(blockIdx.x, gridDim.x), dom, blk);
   const DomDev<T>& D = doms[dom];
   if (D.st->halt) return;
   if (pass == 1 && !D.corrector) return;      // the corrector pass
-  if (l < D.ny) reduce_line<T>(D.cx, D.ny, l, gbl((const T*)D.chx), gbl((const T*)D.rsx), gbl(D.ifx));
-  else reduce_line<T>(D.cy, D.nx, l - D.ny, gbl((const T*)D.chy), gbl((const T*)D.rsy), gbl(D.ify));
-}
-
-// The same recurrences with each line's chunks cut into NS segments (4 or 8),
-// one wave per segment (a block holds 64 lines x NS segments).  Both sweeps are
-// affine recurrences (alpha_c = A_c alpha_{c-1} + B_c forward, with
-// A_c = m1 + m2 k2 and B_c = xh_e + m2 k1 xh_s; X_s(c) = tau_c X_s(c+1) +
-// sigma_c backward), so each segment first composes its maps, the segments
-// exchange them through LDS, and each then runs its part with the right
-// incoming value: twice the arithmetic, 1/NS of the serial length.  The
-// results equal the serial sweep's up to rounding (the composition
-// reassociates the products).
-template <typename T, int NS>
-__device__ __forceinline__ void reduce_line_seg(int C, int L, int line, int seg, bool active, const gp<const T> ch,
-                                                const gp<const T> rs, const gp<T> itf, T (*xa)[64], T (*xb)[64],
-                                                int lane) {
-  // the loads of RB chunks are issued together ahead of their serial steps
-  constexpr int RB = 8;
+  const int nbx = (D.ny + RED_LINES - 1) / RED_LINES;
+  const bool xl = blk < nbx;
+  const int L = uni(xl ? D.ny : D.nx), C = uni(xl ? D.cx : D.cy);
+  const int ln = threadIdx.x % RED_LINES, seg = threadIdx.x / RED_LINES;
+  const int row = seg % RED_ROWS, wave = uni(seg / RED_ROWS);
+  const int line = (xl ? blk : blk - nbx) * RED_LINES + ln;
+  const bool active = line < L;
+  const unsigned lo = (unsigned)min(line, L - 1);
   const size_t CL = (size_t)C * L;
-  const int c0 = (int)(((long long)seg * C) / NS), c1 = (int)(((long long)(seg + 1) * C) / NS);
-  const int n = active ? c1 - c0 : 0;
-  // A segment of at most NB chunks keeps its inputs in registers from one
-  // batch of loads per RB chunks to the end, so the four sweeps below read
-  // no memory after the first, as the per-chunk affine maps
-  // sigma_c = p0 + p1 alpha_{c-1}, alpha_c = pb + pa alpha_{c-1} and the
-  // backward coefficients t4, t5.  Longer segments load again in every
-  // sweep.  (The register file this takes lowers the kernel's occupancy,
-  // which the latency-bound launches of single domains do not feel.)
-  constexpr int NB = sizeof(T) == 4 ? 16 : 8;
-  const bool reg = n <= NB;
-  T p0[NB], p1[NB], pa[NB], pb[NB], t4[NB], t5[NB];
-  // forward, pass 1: the segment's composite map alpha_out = A alpha_in + B
-  T A = T(1), B = T(0);
-  if (reg) {
+  const T* const ch = uni((const T*)(xl ? D.chx : D.chy));
+  const T* const rs = uni((const T*)(xl ? D.rsx : D.rsy));
+  T* const itf = uni(xl ? D.ifx : D.ify);     // left neighbour values
+  T* const itr = itf + CL;                    // right neighbour values
+  const int panels = (C + RED_PANEL - 1) / RED_PANEL;
+  T sg[RED_MAX], al[RED_MAX], t4[RED_MAX], t5[RED_MAX];
+  T a = T(0);                                 // alpha of the chunk before
+  for (int p = 0; p < panels; ++p) {
+    const int c0 = p * RED_PANEL + seg * RED_MAX;
+    const int waves = min(RED_SEGS / RED_ROWS, (C - p * RED_PANEL + RED_MAX * RED_ROWS - 1) / (RED_MAX * RED_ROWS));
+    T k1[RED_MAX], k2[RED_MAX], m1[RED_MAX], m2[RED_MAX], xs[RED_MAX], xe[RED_MAX];
+    if (wave < waves) {
 #pragma unroll
-    for (int b0 = 0; b0 < NB; b0 += RB) {
-      if (b0 < n) {
-        T r0[RB], r1[RB], r2[RB], r3[RB], r4[RB], r5[RB], xs[RB], xe[RB];
+      for (int k = 0; k < RED_MAX; ++k) {
+        const unsigned o = (unsigned)min(c0 + k, C - 1) * (unsigned)L + lo;
+        xs[k] = ldu(ch, o);
+        xe[k] = ldu(ch + CL, o);
+        k1[k] = ldu(rs, o);
+        k2[k] = ldu(rs + CL, o);
+        m1[k] = ldu(rs + 2 * CL, o);
+        m2[k] = ldu(rs + 3 * CL, o);
+        t4[k] = ldu(rs + 4 * CL, o);
+        t5[k] = ldu(rs + 5 * CL, o);
+      }
+    }
+    for (int w = 0; w < waves; ++w) {
+      if (w == wave) {
+        if (w > 0) a = hand[ln];
+        // chunks past the line's last one change only values that are not used
+        auto sweep = [&](auto r) {
+          if (decltype(r)::value == row) {
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-          const size_t o = (size_t)(c0 + min(b0 + k, n - 1)) * L + line;
-          r0[k] = rs[o];
-          r1[k] = rs[CL + o];
-          r2[k] = rs[2 * CL + o];
-          r3[k] = rs[3 * CL + o];
-          r4[k] = rs[4 * CL + o];
-          r5[k] = rs[5 * CL + o];
-          xs[k] = ch[o];
-          xe[k] = ch[CL + o];
-        }
-#pragma unroll
-        for (int k = 0; k < RB; ++k) {
-          const int j = b0 + k;
-          const T q0 = r0[k] * xs[k];
-          p0[j] = q0;
-          p1[j] = r1[k];
-          pa[j] = r2[k] + r3[k] * r1[k];
-          pb[j] = xe[k] + r3[k] * q0;
-          t4[j] = r4[k];
-          t5[j] = r5[k];
-          if (j < n) {
-            A = pa[j] * A;
-            B = pa[j] * B + pb[j];
+            for (int k = 0; k < RED_MAX; ++k) {
+              // (which of the two products is rounded first is part of the result)
+              sg[k] = k == 0 ? fma_(k2[k], a, k1[k] * xs[k]) : fma_(k1[k], xs[k], k2[k] * a);
+              a = fma_(m2[k], sg[k], fma_(m1[k], a, xe[k]));
+              al[k] = a;
+            }
           }
+        };
+        sweep(Int<0>{});
+        a = row_move<true, 0>(a);
+        sweep(Int<1>{});
+        a = row_move<true, 1>(a);
+        sweep(Int<2>{});
+        a = row_move<true, 2>(a);
+        sweep(Int<3>{});
+        if (row == RED_ROWS - 1) hand[ln] = a;
+      }
+      __syncthreads();
+    }
+    a = hand[ln];                             // into the next panel
+    if (p + 1 < panels && active) {
+#pragma unroll
+      for (int k = 0; k < RED_MAX; ++k)
+        if (c0 + k < C) {
+          const unsigned o = (unsigned)(c0 + k) * (unsigned)L + lo;
+          stu(itf, o, sg[k]);
+          stu(itr, o, al[k]);
         }
-      }
     }
+    __syncthreads();
   }
-  for (int b0 = 0; b0 < (reg ? 0 : n); b0 += RB) {
-    T k1[RB], k2[RB], m1[RB], m2[RB], xs[RB], xe[RB];
+  // the chunks past the last one hand it a zero
+  if (panels > 0) {
+    const int c0 = (panels - 1) * RED_PANEL + seg * RED_MAX;
 #pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)(c0 + min(b0 + k, n - 1)) * L + line;
-      k1[k] = rs[o];
-      k2[k] = rs[CL + o];
-      m1[k] = rs[2 * CL + o];
-      m2[k] = rs[3 * CL + o];
-      xs[k] = ch[o];
-      xe[k] = ch[CL + o];
+    for (int k = 0; k < RED_MAX; ++k)
+      if (c0 + k >= C) sg[k] = T(0);
+  }
+  T x = T(0);                                 // X_s of the chunk after
+  for (int p = panels - 1; p >= 0; --p) {
+    const int c0 = p * RED_PANEL + seg * RED_MAX;
+    const int waves = min(RED_SEGS / RED_ROWS, (C - p * RED_PANEL + RED_MAX * RED_ROWS - 1) / (RED_MAX * RED_ROWS));
+    if (p + 1 < panels) {
+#pragma unroll
+      for (int k = 0; k < RED_MAX; ++k) {
+        const unsigned o = (unsigned)(c0 + k) * (unsigned)L + lo;   // whole panels but the last
+        sg[k] = ldu((const T*)itf, o);
+        al[k] = ldu((const T*)itr, o);
+        t4[k] = ldu(rs + 4 * CL, o);
+        t5[k] = ldu(rs + 5 * CL, o);
+        pin(sg[k]);
+      }
+      // a slot's sigma is read before the chunk on its left writes its result there
+      __syncthreads();
     }
+    for (int w = waves - 1; w >= 0; --w) {
+      if (w == wave) {
+        if (w < waves - 1) x = hand[ln];
+        auto sweep = [&](auto r) {
+          if (decltype(r)::value == row) {
 #pragma unroll
-    for (int k = 0; k < RB; ++k)
-      if (b0 + k < n) {
-        const T Ac = m1[k] + m2[k] * k2[k], Bc = xe[k] + m2[k] * k1[k] * xs[k];
-        A = Ac * A;
-        B = Ac * B + Bc;
-      }
-  }
-  xa[seg][lane] = A;
-  xb[seg][lane] = B;
-  __syncthreads();
-  T al = T(0);
-  for (int k = 0; k < seg; ++k) al = xa[k][lane] * al + xb[k][lane];
-  __syncthreads();
-  // forward, pass 2: sigma_c, alpha_c of the segment's chunks (in p0, p1
-  // on the register path)
-  if (reg) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-      if (j < n) {
-        const T sg = p0[j] + p1[j] * al;
-        al = pb[j] + pa[j] * al;
-        p0[j] = sg;
-        p1[j] = al;
-      }
-  }
-  for (int b0 = 0; b0 < (reg ? 0 : n); b0 += RB) {
-    T r0[RB], r1[RB], r2[RB], r3[RB], xs[RB], xe[RB];
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)(c0 + min(b0 + k, n - 1)) * L + line;
-      r0[k] = rs[o];
-      r1[k] = rs[CL + o];
-      r2[k] = rs[2 * CL + o];
-      r3[k] = rs[3 * CL + o];
-      xs[k] = ch[o];
-      xe[k] = ch[CL + o];
-    }
-#pragma unroll
-    for (int k = 0; k < RB; ++k)
-      if (b0 + k < n) {
-        const size_t o = (size_t)(c0 + b0 + k) * L + line;
-        const T sg = r0[k] * xs[k] + r1[k] * al;
-        al = xe[k] + r2[k] * al + r3[k] * sg;
-        itf[o] = sg;
-        itf[CL + o] = al;
-      }
-  }
-  // backward, pass 1: X_s(c0) = R X_s(c1) + S over the segment
-  T R = T(1), Sv = T(0);
-  if (reg) {
-#pragma unroll
-    for (int j = NB - 1; j >= 0; --j)
-      if (j < n) {
-        R = t4[j] * R;
-        Sv = t4[j] * Sv + p0[j];
-      }
-  }
-  for (int b1 = 0; b1 < (reg ? 0 : n); b1 += RB) {
-    T tau[RB], sg[RB];
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)(c1 - 1 - min(b1 + k, n - 1)) * L + line;
-      tau[k] = rs[4 * CL + o];
-      sg[k] = itf[o];
-    }
-#pragma unroll
-    for (int k = 0; k < RB; ++k)
-      if (b1 + k < n) {
-        R = tau[k] * R;
-        Sv = tau[k] * Sv + sg[k];
-      }
-  }
-  xa[seg][lane] = R;
-  xb[seg][lane] = Sv;
-  __syncthreads();
-  T xs_next = T(0);
-  for (int k = NS - 1; k > seg; --k) xs_next = xa[k][lane] * xs_next + xb[k][lane];
-  // backward, pass 2; the left-neighbour value of the next segment's first
-  // chunk is written after the barrier (that segment reads the slot first)
-  T held = T(0);
-  bool hold = false;
-  if (reg) {
-#pragma unroll
-    for (int j = NB - 1; j >= 0; --j)
-      if (j < n) {
-        const int c = c0 + j;
-        const size_t o = (size_t)c * L + line;
-        const T Xs = p0[j] + t4[j] * xs_next;
-        const T Xe = p1[j] + t5[j] * xs_next;
-        itf[CL + o] = xs_next;                    // right neighbour of chunk c
-        if (c + 1 < C) {
-          if (c == c1 - 1) {
-            held = Xe;
-            hold = true;
-          } else {
-            itf[o + L] = Xe;                      // left neighbour of chunk c + 1
+            for (int k = RED_MAX - 1; k >= 0; --k) {
+              const T Xs = fma_(t4[k], x, sg[k]);
+              sg[k] = fma_(t5[k], x, al[k]);            // X_e(c)
+              al[k] = x;
+              x = Xs;
+            }
           }
-        }
-        xs_next = Xs;
+        };
+        sweep(Int<3>{});
+        x = row_move<false, 3>(x);
+        sweep(Int<2>{});
+        x = row_move<false, 2>(x);
+        sweep(Int<1>{});
+        x = row_move<false, 1>(x);
+        sweep(Int<0>{});
+        if (row == 0) hand[ln] = x;
       }
-  }
-  for (int b1 = 0; b1 < (reg ? 0 : n); b1 += RB) {
-    T sg[RB], a[RB], r4[RB], r5[RB];
-#pragma unroll
-    for (int k = 0; k < RB; ++k) {
-      const size_t o = (size_t)(c1 - 1 - min(b1 + k, n - 1)) * L + line;
-      sg[k] = itf[o];
-      a[k] = itf[CL + o];
-      r4[k] = rs[4 * CL + o];
-      r5[k] = rs[5 * CL + o];
+      __syncthreads();
     }
+    x = hand[ln];                             // into the panel before
+    if (active) {
 #pragma unroll
-    for (int k = 0; k < RB; ++k)
-      if (b1 + k < n) {
-        const int c = c1 - 1 - (b1 + k);
-        const size_t o = (size_t)c * L + line;
-        const T Xs = sg[k] + r4[k] * xs_next;
-        const T Xe = a[k] + r5[k] * xs_next;
-        itf[CL + o] = xs_next;                    // right neighbour of chunk c
-        if (c + 1 < C) {
-          if (c == c1 - 1) {
-            held = Xe;
-            hold = true;
-          } else {
-            itf[o + L] = Xe;                      // left neighbour of chunk c + 1
-          }
+      for (int k = 0; k < RED_MAX; ++k)
+        if (c0 + k < C) {
+          const unsigned o = (unsigned)(c0 + k) * (unsigned)L + lo;
+          stu(itr, o, al[k]);                                     // right neighbour of chunk c
+          if (c0 + k + 1 < C) stu(itf, o + (unsigned)L, sg[k]);   // left neighbour of chunk c + 1
         }
-        xs_next = Xs;
-      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  if (hold) itf[(size_t)c1 * L + line] = held;
-  if (active && seg == 0) itf[line] = T(0);       // chunk 0 has no left neighbour
-}
-
-template <typename T, int NS>
-__global__ void __launch_bounds__(64 * NS) k_reduced_seg(const DomDev<T>* __restrict__ doms,
-                                                        const int* __restrict__ line_map, int nd, int lines,
-                                                        int pass) {
-  __shared__ T xa[NS][64], xb[NS][64];
-  const int lane = threadIdx.x & 63, seg = threadIdx.x >> 6;
-  const int gid = blockIdx.x * 64 + lane;
-  // every thread reaches the barriers; inactive ones carry identity maps
-  bool active = gid < lines;
-  int dom = 0, l = 0;
-  if (active) {
-    locate(line_map, nd, gid, dom, l);
-    const DomDev<T>& D = doms[dom];
-    active = !D.st->halt && !(pass == 1 && !D.corrector);
-  }
-  // one call site: the barriers inside must be met by every wave once, and
-  // the lanes of a wave may hold x-lines and y-lines
-  const DomDev<T>& D = doms[dom];
-  const bool xl = l < D.ny;
-  reduce_line_seg<T, NS>(xl ? D.cx : D.cy, xl ? D.ny : D.nx, xl ? l : l - D.ny, seg, active,
-                     gbl((const T*)(xl ? D.chx : D.chy)), gbl((const T*)(xl ? D.rsx : D.rsy)),
-                     gbl(xl ? D.ifx : D.ify), xa, xb, lane);
+  if (active && seg == 0) stu(itf, lo, T(0));   // chunk 0 has no left neighbour
 }
 
 // ---------------------------------------------------------------------------

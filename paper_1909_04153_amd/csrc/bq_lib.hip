@@ -199,7 +199,7 @@ __global__ void k_setup_spikes(const DomDev<T>* Dp, int dir) {
   rs[3 * CL + o] = r[m - 1];
 }
 
-// static coefficients of the interface recurrence (see reduce_line)
+// static coefficients of the interface recurrence (see k_reduced)
 template <typename T>
 __global__ void k_setup_reduced(const DomDev<T>* Dp, int dir) {
   const DomDev<T>& D = *Dp;
@@ -453,16 +453,12 @@ struct Launch {
   // device tables of one launch group (a domain or a batch)
   void* table = nullptr;        // DomDev<T>[nd]
   int* tile_map = nullptr;      // per tile: domain << MAP_SHIFT | tile (batches; NULL for one domain)
-  int* line_map = nullptr;      // per line: domain << MAP_SHIFT | line
+  int* line_map = nullptr;      // per block of lines: domain << MAP_SHIFT | block
   void* status = nullptr;       // StatusRec[nd]: staging of bq_batch_status (batches)
-  int nd = 0, tiles = 0, lines = 0;
+  int nd = 0, tiles = 0, lblocks = 0;
   int ty = 0, mx = 0;           // tile shape shared by the members
   int any_pc = 0;               // some member runs the corrector pass
-  // schedule (tuned per batch): threads per block of the line-coupling
-  // kernel, XCD-aware tile order of the stencil kernel
-  int rblock = 256;
-  int swizzle = 1;
-  int segs = 1;                 // 1: one thread per line; 4 or 8: segmented sweeps
+  int swizzle = 1;              // XCD-aware tile order (schedule, set per batch)
   hipGraphExec_t graph = nullptr;
   int graph_steps = 0;          // steps per replay (0 = none)
   int graph_built = 0;          // steps captured in `graph`
@@ -507,7 +503,8 @@ struct bq_batch {
   hipStream_t lane[MAX_LANES] = {};
   hipEvent_t ev_fork = nullptr, ev_join[MAX_LANES] = {};
   int graph_steps = 16;
-  int rblock = 256, swizzle = 1, segs = 1;  // schedule copied into the launches
+  int swizzle = 1;              // schedule copied into the launches
+  int rblock = 256, segs = 1;   // reported back as they were set (one line-coupling kernel serves all)
   int static_dev = -1;          // >= 0: tables in that device's static array (bq_batch_set_static)
   int ty = 0, mx = 0;           // tile shape of the members (0: the first member's)
 };
@@ -806,7 +803,7 @@ static int create_t(bq_domain* d, const double* depth_c) {
   d->L.nd = 1;
   d->L.any_pc = D.corrector;
   d->L.tiles = D.tiles_x * D.tiles_y;
-  d->L.lines = p->nx + p->ny;
+  d->L.lblocks = line_blocks(p->nx, p->ny);
   d->L.ty = sh0.ty;
   d->L.mx = sh0.mx;
   if (D.n_waves > 0) {
@@ -903,13 +900,7 @@ static int set_shape_t(bq_domain* d, int ty, int mx) {
 
 template <typename T>
 static void launch_reduced(const Launch& L, hipStream_t s, int pass) {
-  const DomDev<T>* tab = (const DomDev<T>*)L.table;
-  if (L.segs == 8)
-    k_reduced_seg<T, 8><<<cdiv(L.lines, 64), 64 * 8, 0, s>>>(tab, L.line_map, L.nd, L.lines, pass);
-  else if (L.segs == 4)
-    k_reduced_seg<T, 4><<<cdiv(L.lines, 64), 64 * 4, 0, s>>>(tab, L.line_map, L.nd, L.lines, pass);
-  else
-    k_reduced<T><<<cdiv(L.lines, L.rblock), L.rblock, 0, s>>>(tab, L.line_map, L.nd, L.lines, pass);
+  k_reduced<T><<<L.lblocks, RED_THREADS, 0, s>>>((const DomDev<T>*)L.table, L.line_map, L.nd, pass);
 }
 
 // the stencil/update kernel (pass 0: AB3 step, 1: corrector) and the
@@ -1164,13 +1155,13 @@ __global__ void k_batch_status(const DomDev<T>* __restrict__ doms, int nd, Statu
 // line map, status staging
 template <typename T>
 static size_t launch_bytes(const std::vector<bq_domain*>& doms) {
-  size_t tiles = 0, lines = 0;
+  size_t tiles = 0, lblocks = 0;
   for (const bq_domain* d : doms) {
     const DomDev<T>& D = desc<T>(const_cast<bq_domain*>(d));
     tiles += (size_t)D.tiles_x * D.tiles_y;
-    lines += (size_t)D.nx + D.ny;
+    lblocks += (size_t)line_blocks(D.nx, D.ny);
   }
-  return rup(sizeof(DomDev<T>) * doms.size(), 256) + rup(sizeof(int) * tiles, 256) + rup(sizeof(int) * lines, 256) +
+  return rup(sizeof(DomDev<T>) * doms.size(), 256) + rup(sizeof(int) * tiles, 256) + rup(sizeof(int) * lblocks, 256) +
          rup(sizeof(StatusRec) * doms.size(), 256);
 }
 
@@ -1184,7 +1175,7 @@ static int fill_launch(Launch& L, char* m, const std::vector<bq_domain*>& doms, 
   std::vector<int> tmap, lmap;
   for (int k = 0; k < nd; ++k) {
     tab[k] = desc<T>(doms[k]);
-    const int nt = tab[k].tiles_x * tab[k].tiles_y, nl = tab[k].nx + tab[k].ny;
+    const int nt = tab[k].tiles_x * tab[k].tiles_y, nl = line_blocks(tab[k].nx, tab[k].ny);
     for (int t = 0; t < nt; ++t) tmap.push_back((k << MAP_SHIFT) | t);
     for (int l = 0; l < nl; ++l) lmap.push_back((k << MAP_SHIFT) | l);
   }
@@ -1201,7 +1192,7 @@ static int fill_launch(Launch& L, char* m, const std::vector<bq_domain*>& doms, 
   L.status = m + tb + mb + lb;
   L.nd = nd;
   L.tiles = (int)tmap.size();
-  L.lines = (int)lmap.size();
+  L.lblocks = (int)lmap.size();
   L.any_pc = 0;
   for (int k = 0; k < nd; ++k) L.any_pc |= tab[k].corrector;
   L.ty = tab[0].my;
@@ -1277,9 +1268,7 @@ static int batch_build_t(bq_batch* b) {
   }
   int rc = fill_launch<T>(b->L, m, b->doms, b->stream, stat);
   if (rc) return rc;
-  b->L.rblock = b->rblock;
   b->L.swizzle = b->swizzle;
-  b->L.segs = b->segs;
   for (int g = 0; g < MAX_LANES; ++g) {
     if (stat) b->G[g].graph_built = 0;
     else drop_graph<T>(b->G[g]);
@@ -1289,9 +1278,7 @@ static int batch_build_t(bq_batch* b) {
     for (int g = 0; g < nl && !rc; ++g) {
       rc = fill_launch<T>(b->G[g], m + off, part[g], b->stream, stat);
       off += sg[g];
-      b->G[g].rblock = b->rblock;
       b->G[g].swizzle = b->swizzle;
-      b->G[g].segs = b->segs;
     }
     if (rc) return rc;
   }
@@ -1435,9 +1422,7 @@ static void apply_schedule(bq_batch* b, int rblock, int swizzle, int segs) {
   Launch* ls[1 + MAX_LANES] = {&b->L};
   for (int g = 0; g < MAX_LANES; ++g) ls[1 + g] = &b->G[g];
   for (Launch* L : ls) {
-    L->rblock = rblock;
     L->swizzle = swizzle;
-    L->segs = segs;
     // graphs hold the launch parameters they were captured with
     graph_del(L->graph);
   }
@@ -1469,8 +1454,8 @@ static int set_tune(bq_batch* b, const bq_tune* t) {
   return BQ_OK;
 }
 
-// Each candidate runs real steps of the method (every schedule gives the
-// same results, bit for bit without segments and up to rounding with them),
+// Each candidate runs real steps of the method (every schedule of one tile
+// shape gives the same results bit for bit),
 // so tuning costs no simulation work: warm-up (which also captures the
 // graph), then steps_per_trial timed steps.
 template <typename T>
@@ -1482,10 +1467,7 @@ static int batch_autotune_t(bq_batch* b, int steps, bq_tune* out) {
   // below the trials' timing noise, so a search would pick it by chance.
   const int ty0 = b->ty, mx0 = b->mx;
   for (int lanes = 1; lanes <= max_lanes; ++lanes)
-    for (int graph : {4, 16}) {
-      for (int rb : {64, 256}) cands.push_back(bq_tune{lanes, graph, rb, 1, 1, ty0, mx0, 0.0});
-      for (int ns : {4, 8}) cands.push_back(bq_tune{lanes, graph, 256, 1, ns, ty0, mx0, 0.0});
-    }
+    for (int graph : {4, 16}) cands.push_back(bq_tune{lanes, graph, b->rblock, 1, b->segs, ty0, mx0, 0.0});
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (event_new(&e0, true) != hipSuccess || event_new(&e1, true) != hipSuccess) {
     event_del(e0);
