@@ -238,12 +238,47 @@ template <typename T> __device__ __forceinline__ T frcp(T x);
 template <typename T> __device__ __forceinline__ T frcbrt(T x);   // x^(-1/3), x > 0
 template <> __device__ __forceinline__ double fsqrt<double>(double x) { return sqrt(x); }
 template <> __device__ __forceinline__ double frcp<double>(double x) { return 1.0 / x; }
-template <> __device__ __forceinline__ double frcbrt<double>(double x) { return 1.0 / cbrt(x); }
+// FP64: from the FP32 value (about 1e-6) by two steps of y += y (1 - x y^3) / 3
+// (Newton's, quadratic: 1e-12, then rounding); outside the FP32 range by the
+// library's cube root
+template <> __device__ __forceinline__ double frcbrt<double>(double x) {
+  if (!(x > 1e-30 && x < 1e30)) return 1.0 / cbrt(x);
+  double y = (double)__builtin_amdgcn_exp2f(-0.33333333f * __builtin_amdgcn_logf((float)x));
+  y = __builtin_fma(y * (1.0 / 3.0), __builtin_fma(-x * y, y * y, 1.0), y);
+  return __builtin_fma(y * (1.0 / 3.0), __builtin_fma(-x * y, y * y, 1.0), y);
+}
 template <> __device__ __forceinline__ float fsqrt<float>(float x) { return __builtin_amdgcn_sqrtf(x); }
 template <> __device__ __forceinline__ float frcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
-// a / b: correctly rounded in FP64, reciprocal-multiply in FP32
-__device__ __forceinline__ double fdiv(double a, double b) { return a / b; }
-__device__ __forceinline__ float fdiv(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
+// Reciprocal, square root and inverse square root of a positive number.  FP64:
+// the hardware's approximation (2^-24) refined to about 1 ulp, without the
+// scaling and the special cases of the correctly rounded operations (5, 8
+// and 8 instructions against 11, 18 and, as a division by a root, 29).
+__device__ __forceinline__ float rcp_n(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float sqrt_n(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ __forceinline__ double rcp_n(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
+// one coupled step for s = sqrt(x) and h = 1 / (2 sqrt(x))
+__device__ __forceinline__ void root_step(double x, double& s, double& h) {
+  const double y = __builtin_amdgcn_rsq(x);
+  s = x * y;
+  h = 0.5 * y;
+  const double r = __builtin_fma(-h, s, 0.5);
+  s = __builtin_fma(s, r, s);
+  h = __builtin_fma(h, r, h);
+}
+__device__ __forceinline__ double sqrt_n(double x) {
+  double s, h;
+  root_step(x, s, h);
+  return __builtin_fma(__builtin_fma(-s, s, x), h, s);
+}
+__device__ __forceinline__ double half_rsq_n(double x) {   // 1 / (2 sqrt(x))
+  double s, h;
+  root_step(x, s, h);
+  return __builtin_fma(h, __builtin_fma(-h, s, 0.5), h);
+}
 // The hardware log takes a subnormal input as 0 (giving +inf here, and a
 // NaN once multiplied by the zero velocity of a film that thin): depths are
 // raised to the smallest normal value first, which leaves h^(-1/3) finite
@@ -285,7 +320,7 @@ template <typename T>
 __device__ __forceinline__ T vfac(T h, T eps) {
   const T h2 = h * h;
   const T h4 = h2 * h2;
-  if (h4 >= eps) return frcp(h);
+  if (h4 >= eps) return rcp_n(h);
   return T(1.4142135623730951) * h * frcp(fsqrt(h4 + eps));
 }
 
@@ -330,13 +365,10 @@ __device__ __forceinline__ float dmax_nq<float>(float a, float b) {
   return __builtin_amdgcn_fmed3f(a, b, 3.402823466e38f);
 }
 
-// Piecewise-linear w at a cell's low/high faces with the KP07 positivity
-// correction; Dlo/Dhi are the still-water depths at the faces (bed = -D).
-template <bool LIM, typename T>
-__device__ __forceinline__ void recon_w(T wm, T w0, T wp, T ht, T Dlo, T Dhi, T& wlo, T& whi) {
-  const T s = hslope<LIM>(wm, w0, wp, ht);
-  wlo = w0 - s;
-  whi = w0 + s;
+// KP07 positivity correction of the surface w0 -/+ slope at a cell's low/high
+// faces; Dlo/Dhi are the still-water depths there (bed = -D)
+template <typename T>
+__device__ __forceinline__ void positive(T w0, T Dlo, T Dhi, T& wlo, T& whi) {
   if (whi + Dhi < T(0)) {
     whi = -Dhi;
     wlo = T(2) * w0 + Dhi;
@@ -344,6 +376,17 @@ __device__ __forceinline__ void recon_w(T wm, T w0, T wp, T ht, T Dlo, T Dhi, T&
     wlo = -Dlo;
     whi = T(2) * w0 + Dlo;
   }
+}
+
+template <typename T>
+__device__ __forceinline__ T fma_(T a, T b, T c);
+template <>
+__device__ __forceinline__ float fma_<float>(float a, float b, float c) {
+  return __builtin_fmaf(a, b, c);
+}
+template <>
+__device__ __forceinline__ double fma_<double>(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
 }
 
 // One side of a face.  The hydrostatic pressure g h^2 / 2 is carried as its
@@ -354,65 +397,96 @@ __device__ __forceinline__ void recon_w(T wm, T w0, T wp, T ht, T Dlo, T Dhi, T&
 // source cancel exactly except in cells whose two faces straddle the
 // still-water line (see add_shore); keeping them would leave FP32 with a
 // difference of large numbers in deep water.
+//
+// The face pass below takes a straight form where a wave's sides are all
+// deep and this general one elsewhere, and a cell's result must not depend on
+// which of them its wave took (rows of one wave front would differ, and the
+// quadratic F* extrapolation amplifies that).  So both forms write their fused
+// multiply-adds out, with contraction off, and compute a deep side (h^4 >=
+// eps) by the same expressions.
 template <typename T>
 struct Side {
-  T w, h, un, ut, qn, qt, dev, pp;
+  T w, h, un, ut, qn, qt, dev, pa, pb, c;      // pp = pa * pb, c = sqrt(g h)
 };
 
-template <typename T>
-__device__ __forceinline__ Side<T> make_side(T w, T qn, T qt, T Dface, T eps, T g) {
-  Side<T> s;
-  s.w = w;
-  s.h = fmax(w + Dface, T(0));
-  const T h2 = s.h * s.h;
-  const T h4 = h2 * h2;
-  // FP32: for h^4 >= eps, u = q / h and the recomputed discharge h u is q
-  // itself (exact identities); FP64 evaluates the general expression, so
-  // that at wet/dry fronts it rounds like the FP64 reference
-  if (sizeof(T) == 4 && h4 >= eps) {
-    const T vf = frcp(s.h);
+// velocities, recomputed discharges h u and wave speed of a side, DEEP: known
+// to have h^4 >= eps.  u = sqrt(2) h q / sqrt(h^4 + max(h^4, eps)).
+__device__ __forceinline__ void side_speeds(Side<float>& s, float qn, float qt, float eps, float g) {
+#pragma clang fp contract(off)
+  const float h2 = s.h * s.h;
+  const float h4 = h2 * h2;
+  if (h4 >= eps) {
+    // u = q / h, and h u is q itself (exact identities)
+    const float vf = rcp_n(s.h);
     s.un = qn * vf;
     s.ut = qt * vf;
     s.qn = qn;
     s.qt = qt;
   } else {
-    // u = sqrt(2) h q / sqrt(h^4 + max(h^4, eps)), recomputed discharge h u
-    const T den = fsqrt(h4 + fmax(h4, eps));
-    const T sh = T(1.4142135623730951) * s.h;
-    s.un = fdiv(sh * qn, den);
-    s.ut = fdiv(sh * qt, den);
+    const float r = __builtin_amdgcn_rsqf(h4 + fmax(h4, eps));
+    const float sh = 1.4142135623730951f * s.h;
+    s.un = sh * qn * r;
+    s.ut = sh * qt * r;
     s.qn = s.h * s.un;
     s.qt = s.h * s.ut;
   }
+  s.c = sqrt_n(g * s.h);
+}
+// FP64 keeps the one expression everywhere, so that at wet/dry fronts it
+// rounds like the FP64 reference
+template <bool DEEP = false>
+__device__ __forceinline__ void side_speeds(Side<double>& s, double qn, double qt, double eps, double g) {
+#pragma clang fp contract(off)
+  const double h2 = s.h * s.h;
+  const double h4 = h2 * h2;
+  const double vf = 2.8284271247461901 * s.h * half_rsq_n(h4 + (DEEP ? h4 : fmax(h4, eps)));
+  s.un = qn * vf;
+  s.ut = qt * vf;
+  s.qn = s.h * s.un;
+  s.qt = s.h * s.ut;
+  const double gh = g * s.h, c = sqrt_n(gh);
+  s.c = DEEP || gh > 0.0 ? c : 0.0;
+}
+
+template <typename T>
+__device__ __forceinline__ Side<T> make_side(T w, T qn, T qt, T Dface, T eps, T g) {
+#pragma clang fp contract(off)
+  Side<T> s;
+  s.w = w;
+  s.h = fmax(w + Dface, T(0));
+  side_speeds(s, qn, qt, eps, g);
   const T Dp = dpos(Dface);
   // (h > 0 exactly when w > -D, so below the still-water line dev is max(w, -D))
   s.dev = Dface > T(0) ? dmax_nq(w, -Dface) : s.h;
-  s.pp = T(0.5) * g * s.dev * (s.h + Dp);
+  s.pa = T(0.5) * g * s.dev;
+  s.pb = s.h + Dp;
   return s;
 }
 
 // central-upwind flux normal to a face, components (mass, normal momentum,
-// tangential momentum); the normal momentum flux excludes g D^2 / 2
-template <typename T>
+// tangential momentum); the normal momentum flux excludes g D^2 / 2.  DEEP:
+// both sides are deep, so at least one of the speeds is not zero.
+template <bool DEEP, typename T>
 __device__ __forceinline__ void cu_flux(const Side<T>& L, const Side<T>& R, T g, T Dface, T& f0, T& fn, T& ft) {
-  const T cL = fsqrt(g * L.h), cR = fsqrt(g * R.h);
-  const T ap = fmax(fmax(L.un + cL, R.un + cR), T(0));
-  const T am = fmin(fmin(L.un - cL, R.un - cR), T(0));
+#pragma clang fp contract(off)
+  const T ap = fmax(fmax(L.un + L.c, R.un + R.c), T(0));
+  const T am = fmin(fmin(L.un - L.c, R.un - R.c), T(0));
   const T den = ap - am;
-  if (den == T(0)) {
+  if (!DEEP && den == T(0)) {
     // both sides dry and at rest: the full flux is zero
     const T Dp = dpos(Dface);
     f0 = ft = T(0);
     fn = -T(0.5) * g * Dp * Dp;
     return;
   }
-  const T inv = frcp(den);
+  const T inv = rcp_n(den);
   const T dis = ap * am * inv;
-  const T pL = L.qn * L.un + L.pp;
-  const T pR = R.qn * R.un + R.pp;
-  f0 = (ap * L.qn - am * R.qn) * inv + dis * (R.w - L.w);
-  fn = (ap * pL - am * pR) * inv + dis * (R.qn - L.qn);
-  ft = (ap * L.qn * L.ut - am * R.qn * R.ut) * inv + dis * (R.qt - L.qt);
+  const T pL = fma_(L.pa, L.pb, L.qn * L.un);
+  const T pR = fma_(R.pa, R.pb, R.qn * R.un);
+  const T aq = ap * L.qn, mq = am * R.qn;
+  f0 = fma_(fma_(ap, L.qn, -mq), inv, dis * (R.w - L.w));
+  fn = fma_(fma_(ap, pL, -(am * pR)), inv, dis * (R.qn - L.qn));
+  ft = fma_(fma_(aq, L.ut, -(mq * R.ut)), inv, dis * (R.qt - L.qt));
 }
 
 // still-water remainder of (bed source - pressure flux difference) in a cell
@@ -424,6 +498,113 @@ __device__ __forceinline__ void add_shore(T& bed, T Dl, T Dh, T g) {
   if (__builtin_expect((Dl > T(0)) != (Dh > T(0)), 0)) {
     const T pl = dpos(Dl), ph = dpos(Dh);
     bed += T(0.5) * g * ((Dh - Dl) * (ph + pl) - (ph * ph - pl * pl));
+  }
+}
+
+// Faces of N consecutive cells of a line (stride st in the tile; w, qn, qt at
+// the second cell before the first): cells -1 .. N are reconstructed once,
+// the N + 1 faces between them taken once, and each cell gets its flux
+// differences (low face less high) plus the well-balanced bed source
+// -g h b_x with h the mean of its own face depths (with the still-water parts
+// of the pressure fluxes taken out only the face-depth departures remain),
+// all times dx: e (mass), n (normal momentum), t (tangential).  Df[k] is the
+// still-water depth of face k - 1.
+//
+// What bounds it is issue, and in small domains (one wave per SIMD) latency:
+// dry and thin sides, the positivity correction and shore faces each take a
+// branch, about eleven a cell, between short dependent runs.  In FP64, whose
+// roots and divisions are those runs, a wave whose sides are all deep and
+// whose faces all lie below the still-water line takes a straight form
+// without any of them: x- and y-faces of a 200 x 20 domain 10.6 -> 6.6
+// thousand cycles; the stencil kernel, with the roots and reciprocals at less than
+// the correctly rounded cost, 13.0 -> 11.3 us there, 19.9 -> 18.0 on
+// 1024 x 256 and 26.9 -> 22.9 on 601 x 601.  (The fields' padding past a domain's end continues its
+// depth, so the tiles there take it too.)  FP32 does without: the test and
+// the second form cost its mixed tiles (a beach's) 5 to 10 % of the kernel,
+// more than they give the deep ones.
+template <typename T, int N>
+__device__ __forceinline__ void face_pass(const T* w, const T* qn, const T* qt, int st, const T (&Df)[N + 3], T ht,
+                                          T eps, T g, T (&e)[N], T (&n)[N], T (&t)[N]) {
+#pragma clang fp contract(off)
+  // cell k - 1 at its low (l) and high (h) faces; limited (theta > 0) or
+  // central slopes: one uniform branch per tile
+  T wl[N + 2], wh[N + 2], pl[N + 2], ph[N + 2], ql[N + 2], qh[N + 2];
+  auto recon = [&](auto lim) {
+    constexpr bool LIM = decltype(lim)::value;
+    auto ends = [&](const T* q, T& lo, T& hi) {
+      const T s = hslope<LIM>(q[0], q[st], q[2 * st], ht);
+      lo = q[st] - s;
+      hi = q[st] + s;
+    };
+#pragma unroll
+    for (int k = 0; k < N + 2; ++k) {
+      ends(w + k * st, wl[k], wh[k]);
+      if (sizeof(T) == 4) positive(w[(k + 1) * st], Df[k], Df[k + 1], wl[k], wh[k]);
+      ends(qn + k * st, pl[k], ph[k]);
+      ends(qt + k * st, ql[k], qh[k]);
+    }
+  };
+  if (ht > T(0)) recon(std::true_type{});
+  else recon(std::false_type{});
+  T f0w = T(0), fnw = T(0), ftw = T(0), dvw = T(0);    // low face of the cell being closed
+  if constexpr (sizeof(T) == 8) {
+    T dmin = Df[0], hmin = wl[0] + Df[0];
+#pragma unroll
+    for (int k = 0; k < N + 2; ++k) {
+      dmin = fmin(dmin, Df[k + 1]);
+      hmin = fmin(hmin, fmin(wl[k] + Df[k], wh[k] + Df[k + 1]));
+    }
+    const T h2 = hmin * hmin;
+    if (__all(dmin > T(0) && hmin > T(0) && h2 * h2 >= eps)) {
+#pragma unroll
+      for (int m = 0; m <= N; ++m) {
+        const T D = Df[m + 1];
+        auto side = [&](T ws, T a, T b) {
+#pragma clang fp contract(off)
+          Side<T> s;
+          s.w = s.dev = ws;
+          s.h = ws + D;
+          side_speeds<true>(s, a, b, eps, g);
+          s.pa = T(0.5) * g * ws;
+          s.pb = s.h + D;
+          return s;
+        };
+        const Side<T> L = side(wh[m], ph[m], qh[m]), R = side(wl[m + 1], pl[m + 1], ql[m + 1]);
+        T f0, fn, ft;
+        cu_flux<true>(L, R, g, D, f0, fn, ft);
+        if (m > 0) {
+          const T bed = g * (D - Df[m]) * (T(0.5) * (wh[m] + wl[m]));
+          e[m - 1] = f0w - f0;
+          n[m - 1] = bed - (fn - fnw);
+          t[m - 1] = ftw - ft;
+        }
+        f0w = f0;
+        fnw = fn;
+        ftw = ft;
+      }
+      return;
+    }
+#pragma unroll
+    for (int k = 0; k < N + 2; ++k) positive(w[(k + 1) * st], Df[k], Df[k + 1], wl[k], wh[k]);
+  }
+#pragma unroll
+  for (int m = 0; m <= N; ++m) {
+    const T D = Df[m + 1];
+    const Side<T> L = make_side(wh[m], ph[m], qh[m], D, eps, g);
+    const Side<T> R = make_side(wl[m + 1], pl[m + 1], ql[m + 1], D, eps, g);
+    T f0, fn, ft;
+    cu_flux<false>(L, R, g, D, f0, fn, ft);
+    if (m > 0) {
+      T bed = g * (D - Df[m]) * (T(0.5) * (L.dev + dvw));
+      add_shore(bed, Df[m], D, g);
+      e[m - 1] = f0w - f0;
+      n[m - 1] = bed - (fn - fnw);
+      t[m - 1] = ftw - ft;
+    }
+    f0w = f0;
+    fnw = fn;
+    ftw = ft;
+    dvw = R.dev;
   }
 }
 
@@ -552,7 +733,7 @@ __device__ __forceinline__ void group_solve_(const T* Dl, int ds, int m, const T
         y = r - l * y_prev;
         sw = -l * s_prev;
       }
-      const T iu = frcp(u);
+      const T iu = rcp_n(u);
       cu[j] = c * iu;
       x[j] = y * iu;
       wv[j] = sw * iu;
@@ -626,12 +807,13 @@ __device__ __forceinline__ void group_solve_(const T* Dl, int ds, int m, const T
   }
   // Gaussian elimination (the matrix is the identity plus coupling
   // responses below one in size: no pivoting)
+  T id[N];
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    const T id = fdiv(T(1), M[e][e]);
+    id[e] = rcp_n(M[e][e]);
 #pragma unroll
     for (int f = e + 1; f < N; ++f) {
-      const T l = M[f][e] * id;
+      const T l = M[f][e] * id[e];
 #pragma unroll
       for (int g = e; g < N; ++g) M[f][g] -= l * M[e][g];
       rv[f] -= l * rv[e];
@@ -643,7 +825,7 @@ __device__ __forceinline__ void group_solve_(const T* Dl, int ds, int m, const T
     T t = rv[e];
 #pragma unroll
     for (int f = e + 1; f < N; ++f) t -= M[e][f] * z[f];
-    z[e] = fdiv(t, M[e][e]);
+    z[e] = t * id[e];
   }
   T Rp = T(0), Lm = T(0);                      // R_part, L_{part-1}
 #pragma unroll
@@ -715,7 +897,7 @@ __device__ __forceinline__ void group_response_(const T* Dl, int ds, int m, cons
         u = b - l * c_prev;
         y = -l * y_prev;
       }
-      const T iu = frcp(u);
+      const T iu = rcp_n(u);
       cu[j] = c * iu;
       f[j] = y * iu;
       if (j == mh - 1) {
@@ -784,12 +966,13 @@ __device__ __forceinline__ void group_response_(const T* Dl, int ds, int m, cons
       rv[2 * i + 1] = gxF[i + 1];
     }
   }
+  T id[N];
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    const T id = fdiv(T(1), M[e][e]);
+    id[e] = rcp_n(M[e][e]);
 #pragma unroll
     for (int q = e + 1; q < N; ++q) {
-      const T l = M[q][e] * id;
+      const T l = M[q][e] * id[e];
 #pragma unroll
       for (int h = e; h < N; ++h) M[q][h] -= l * M[e][h];
       rv[q] -= l * rv[e];
@@ -801,7 +984,7 @@ __device__ __forceinline__ void group_response_(const T* Dl, int ds, int m, cons
     T t = rv[e];
 #pragma unroll
     for (int q = e + 1; q < N; ++q) t -= M[e][q] * z[q];
-    z[e] = fdiv(t, M[e][e]);
+    z[e] = t * id[e];
   }
   T Rp = T(0), Lm = T(0);
 #pragma unroll
@@ -1354,115 +1537,70 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
       pin(fsG[k]);
     }
   }
+  // AB3 history terms alpha_1 X^{n-1} + alpha_2 X^{n-2} (Eq. 42), the
+  // corrector's gamma_1 X^n + gamma_2 X^{n-1} + gamma_3 X^{n-2}.  FP64 forms
+  // them here: the loads have had the F* phase to arrive, and the face passes
+  // then run with 24 registers in the place of 64 (1024 x 256: 19.9 -> 18.4
+  // us); FP32 after the face passes, where they cost it nothing.
+  T hE[CPT], hF[CPT], hG[CPT];
+  auto history = [&]() {
+    const T a1 = (T)sa1, a2 = (T)sa2;
+    const T a3 = CORR ? (T)sa3 : T(0);
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+      hE[k] = a1 * e1.v[k] + a2 * e2.v[k];
+      hF[k] = a1 * f1.v[k] + a2 * f2.v[k];
+      hG[k] = a1 * g1.v[k] + a2 * g2.v[k];
+      if (CORR) {
+        hE[k] += a3 * e3.v[k];
+        hF[k] += a3 * f3.v[k];
+        hG[k] += a3 * g3.v[k];
+      }
+      hF[k] += fsF[k];
+      hG[k] += fsG[k];
+    }
+  };
+  if constexpr (sizeof(T) == 8) {
+    history();
+#pragma unroll
+    for (int k = 0; k < CPT; ++k) {
+      pin(hE[k]);
+      pin(hF[k]);
+      pin(hG[k]);
+    }
+  }
   __syncthreads();
   const T g = D.g, eps = D.eps, ht = T(0.5) * D.theta;
   const T idx = D.idx, idy = D.idy;
   // ---- phase 1x: x-faces by row segments, kept in registers -----------------
-  // The thread's own cells: it reconstructs cells vc-1 .. vc+CPT once, takes
-  // the CPT+1 faces between them (the last one is also its right
-  // neighbour's first) and keeps the x-parts of its cells' E, F, G (flux
-  // differences plus the x bed-slope source).
+  // The thread's own cells (the last face is also its right neighbour's
+  // first); it keeps the x-parts of its cells' E, F, G.
   T acc_e[CPT], acc_f[CPT], acc_g[CPT];
   {
-    const T* wr = sm.w + (vr + 2) * LW + vc;          // tile column vc = cell vc - 2
-    const T* pr = sm.p + (vr + 2) * LW + vc;
-    const T* qr = sm.q + (vr + 2) * LW + vc;
     const T* c0 = sm.dc + (vr + 2) * CP + vc + 1;     // corners of face vc - 1
     T Dfx[CPT + 3];                                   // still-water depth of face vc - 1 + k
 #pragma unroll
     for (int k = 0; k < CPT + 3; ++k) Dfx[k] = T(0.5) * (c0[k] + c0[k + CP]);
-    // cell vc - 1 + k at its low (l) and high (h) faces
-    T wl[CPT + 2], wh[CPT + 2], pl[CPT + 2], ph[CPT + 2], ql[CPT + 2], qh[CPT + 2];
-    // limited (theta > 0) or central slopes: one uniform branch per tile
-    auto recon = [&](auto lim) {
-      constexpr bool LIM = decltype(lim)::value;
-#pragma unroll
-      for (int k = 0; k < CPT + 2; ++k) {
-        recon_w<LIM>(wr[k], wr[k + 1], wr[k + 2], ht, Dfx[k], Dfx[k + 1], wl[k], wh[k]);
-        const T sp = hslope<LIM>(pr[k], pr[k + 1], pr[k + 2], ht);
-        const T sq = hslope<LIM>(qr[k], qr[k + 1], qr[k + 2], ht);
-        pl[k] = pr[k + 1] - sp;
-        ph[k] = pr[k + 1] + sp;
-        ql[k] = qr[k + 1] - sq;
-        qh[k] = qr[k + 1] + sq;
-      }
-    };
-    if (ht > T(0)) recon(std::true_type{});
-    else recon(std::false_type{});
-    T f0w = T(0), fnw = T(0), ftw = T(0), dvw = T(0);  // west face of the cell being closed
-#pragma unroll
-    for (int m = 0; m <= CPT; ++m) {
-      // face vc + m between cells vc + m - 1 (k = m) and vc + m (k = m + 1)
-      const T Df = Dfx[m + 1];
-      const Side<T> L = make_side(wh[m], ph[m], qh[m], Df, eps, g);
-      const Side<T> R = make_side(wl[m + 1], pl[m + 1], ql[m + 1], Df, eps, g);
-      T f0, fn, ft;
-      cu_flux(L, R, g, Df, f0, fn, ft);
-      if (m > 0) {
-        // cell vc + m - 1: well-balanced bed source -g h b_x with h the mean
-        // of its own face depths; with the still-water parts of the pressure
-        // fluxes taken out only the face-depth departures remain
-        const T Dw = Dfx[m], De = Dfx[m + 1];
-        T bed = g * (De - Dw) * (T(0.5) * (L.dev + dvw));
-        add_shore(bed, Dw, De, g);
-        acc_e[m - 1] = -(f0 - f0w) * idx;
-        acc_f[m - 1] = (bed - (fn - fnw)) * idx;
-        acc_g[m - 1] = -(ft - ftw) * idx;
-      }
-      f0w = f0;
-      fnw = fn;
-      ftw = ft;
-      dvw = R.dev;
-    }
+    const int o = (vr + 2) * LW + vc;                 // tile column vc = cell vc - 2
+    face_pass<T, CPT>(sm.w + o, sm.p + o, sm.q + o, 1, Dfx, ht, eps, g, acc_e, acc_f, acc_g);
   }
   // ---- phase 1y: y-faces by column segments, parts to LDS -------------------
   // normal = Q, tangential = P; thread cells (rY0 + q, cY)
   {
     const int cY = tid % TX, rY0 = (tid / TX) * CPT;
-    const T* wc = sm.w + rY0 * LW + cY + 2;           // tile row rY0 = row rY0 - 2
-    const T* pc = sm.p + rY0 * LW + cY + 2;
-    const T* qc = sm.q + rY0 * LW + cY + 2;
     const T* c0 = sm.dc + (rY0 + 1) * CP + cY + 2;    // corners of face rY0 - 1
     T Dfy[CPT + 3];
 #pragma unroll
     for (int k = 0; k < CPT + 3; ++k) Dfy[k] = T(0.5) * (c0[k * CP] + c0[k * CP + 1]);
-    T wl[CPT + 2], wh[CPT + 2], pl[CPT + 2], ph[CPT + 2], ql[CPT + 2], qh[CPT + 2];
-    auto recon = [&](auto lim) {
-      constexpr bool LIM = decltype(lim)::value;
+    const int o = rY0 * LW + cY + 2;                  // tile row rY0 = row rY0 - 2
+    T ye[CPT], yg[CPT], yf[CPT];
+    face_pass<T, CPT>(sm.w + o, sm.q + o, sm.p + o, LW, Dfy, ht, eps, g, ye, yg, yf);
 #pragma unroll
-      for (int k = 0; k < CPT + 2; ++k) {
-        recon_w<LIM>(wc[k * LW], wc[(k + 1) * LW], wc[(k + 2) * LW], ht, Dfy[k], Dfy[k + 1], wl[k], wh[k]);
-        const T sp = hslope<LIM>(pc[k * LW], pc[(k + 1) * LW], pc[(k + 2) * LW], ht);
-        const T sq = hslope<LIM>(qc[k * LW], qc[(k + 1) * LW], qc[(k + 2) * LW], ht);
-        pl[k] = pc[(k + 1) * LW] - sp;
-        ph[k] = pc[(k + 1) * LW] + sp;
-        ql[k] = qc[(k + 1) * LW] - sq;
-        qh[k] = qc[(k + 1) * LW] + sq;
-      }
-    };
-    if (ht > T(0)) recon(std::true_type{});
-    else recon(std::false_type{});
-    T f0s = T(0), fns = T(0), fts = T(0), dvs = T(0);
-#pragma unroll
-    for (int m = 0; m <= CPT; ++m) {
-      const T Df = Dfy[m + 1];
-      const Side<T> Sd = make_side(wh[m], qh[m], ph[m], Df, eps, g);
-      const Side<T> Nd = make_side(wl[m + 1], ql[m + 1], pl[m + 1], Df, eps, g);
-      T f0, fn, ft;
-      cu_flux(Sd, Nd, g, Df, f0, fn, ft);
-      if (m > 0) {
-        const T Ds = Dfy[m], Dn = Dfy[m + 1];
-        T bed = g * (Dn - Ds) * (T(0.5) * (Sd.dev + dvs));
-        add_shore(bed, Ds, Dn, g);
-        const int o = (rY0 + m - 1) * AXP + cY;
-        sm.x.ay[0][o] = -(f0 - f0s) * idy;
-        sm.x.ay[1][o] = -(ft - fts) * idy;            // x-momentum through y-faces
-        sm.x.ay[2][o] = (bed - (fn - fns)) * idy;     // y-momentum
-      }
-      f0s = f0;
-      fns = fn;
-      fts = ft;
-      dvs = Nd.dev;
+    for (int k = 0; k < CPT; ++k) {
+      const int oy = (rY0 + k) * AXP + cY;
+      sm.x.ay[0][oy] = ye[k] * idy;
+      sm.x.ay[1][oy] = yf[k] * idy;                   // x-momentum through y-faces
+      sm.x.ay[2][oy] = yg[k] * idy;                   // y-momentum
     }
   }
   __syncthreads();
@@ -1482,26 +1620,7 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
   static_assert(S::AXP == TXP, "U*, V* alias the y-parts cell by cell");
   const bool row_in = j0 + vr < ny;
   const bool all_in = row_in && i0 + vc + CPT <= nx;
-  // AB3 history terms alpha_1 X^{n-1} + alpha_2 X^{n-2} (Eq. 42), the
-  // corrector's gamma_1 X^n + gamma_2 X^{n-1} + gamma_3 X^{n-2}
-  T hE[CPT], hF[CPT], hG[CPT];
-  {
-    const T a1 = (T)sa1, a2 = (T)sa2;
-    const T a3 = CORR ? (T)sa3 : T(0);
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-      hE[k] = a1 * e1.v[k] + a2 * e2.v[k];
-      hF[k] = a1 * f1.v[k] + a2 * f2.v[k];
-      hG[k] = a1 * g1.v[k] + a2 * g2.v[k];
-      if (CORR) {
-        hE[k] += a3 * e3.v[k];
-        hF[k] += a3 * f3.v[k];
-        hG[k] += a3 * g3.v[k];
-      }
-      hF[k] += fsF[k];
-      hG[k] += fsG[k];
-    }
-  }
+  if constexpr (sizeof(T) == 4) history();
   // eta = w + min(D, 0) over the radius-2 tile, formed once per cell for the
   // dispersive stencils below (in the staging's cell mapping) into the
   // corner tile's words, which nothing reads after the face passes; the
@@ -1533,9 +1652,9 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
     const bool in = row_in & (i0 + c < nx);
     const int C0 = (r + 2) * LW + c + 2;   // radius-2 tile index of the cell
     const int o = r * AXP + c;
-    T e_ = acc_e[k] + sm.x.ay[0][o];
-    T f_ = acc_f[k] + sm.x.ay[1][o];
-    T g_ = acc_g[k] + sm.x.ay[2][o];
+    T e_ = fma_(acc_e[k], idx, sm.x.ay[0][o]);
+    T f_ = fma_(acc_f[k], idx, sm.x.ay[1][o]);
+    T g_ = fma_(acc_g[k], idx, sm.x.ay[2][o]);
     const T d0 = sm.db[C0];
     const T dxm = sm.db[C0 - 1], dxp = sm.db[C0 + 1];
     const T dym = sm.db[C0 - LW], dyp = sm.db[C0 + LW];
@@ -1731,17 +1850,6 @@ using Int = std::integral_constant<int, V>;
 // blocks of RED_LINES lines of a domain: its x-lines', then its y-lines'
 __host__ __device__ inline int line_blocks(int nx, int ny) {
   return (ny + RED_LINES - 1) / RED_LINES + (nx + RED_LINES - 1) / RED_LINES;
-}
-
-template <typename T>
-__device__ __forceinline__ T fma_(T a, T b, T c);
-template <>
-__device__ __forceinline__ float fma_<float>(float a, float b, float c) {
-  return __builtin_fmaf(a, b, c);
-}
-template <>
-__device__ __forceinline__ double fma_<double>(double a, double b, double c) {
-  return __builtin_fma(a, b, c);
 }
 
 // A wave's value moved by one row of 16 lanes: up (row r to row r + 1) for

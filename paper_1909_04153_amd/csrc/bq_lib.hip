@@ -123,17 +123,19 @@ static void graph_del(hipGraphExec_t& x) {
 // ---------------------------------------------------------------------------
 
 // corner still-water depth with two mirrored ghost layers, from io (FP64
-// (ny+1) x (nx+1) host copy)
+// (ny+1) x (nx+1) host copy); the padding to whole tiles (w x h corners)
+// repeats the outermost ghost layer, which only reaches cells outside the
+// domain and keeps the stencil kernel's last tiles as deep as their domain
 template <typename T>
-__global__ void k_setup_corners(const DomDev<T>* Dp) {
+__global__ void k_setup_corners(const DomDev<T>* Dp, int w, int h) {
   const DomDev<T>& D = *Dp;
-  const int w = D.nx + 5, h = D.ny + 5;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= w * h) return;
-  const int ic = e % w - 2, jc = e / w - 2;
+  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= (long long)w * h) return;
+  const int px = (int)(e % w), py = (int)(e / w);
+  const int ic = min(px - 2, D.nx + 2), jc = min(py - 2, D.ny + 2);
   const int mi = ic < 0 ? -ic : (ic > D.nx ? 2 * D.nx - ic : ic);
   const int mj = jc < 0 ? -jc : (jc > D.ny ? 2 * D.ny - jc : jc);
-  D.Dc[(size_t)(jc + 2) * D.cpitch + ic + 2] = (T)D.io[(size_t)mj * (D.nx + 1) + mi];
+  D.Dc[(size_t)py * D.cpitch + px] = (T)D.io[(size_t)mj * (D.nx + 1) + mi];
 }
 
 template <typename T>
@@ -820,8 +822,8 @@ static int create_t(bq_domain* d, const double* depth_c) {
   const size_t nc = (size_t)(p->nx + 1) * (p->ny + 1);
   HIPCHK(hipMemcpyAsync(D.io, depth_c, nc * sizeof(double), hipMemcpyHostToDevice, s));
   const DomDev<T>* Dd = (const DomDev<T>*)d->ddev;
-  const int ncorn = (p->nx + 5) * (p->ny + 5);
-  k_setup_corners<T><<<cdiv(ncorn, 256), 256, 0, s>>>(Dd);
+  const int cw = Ly.tiles_x * TX + 5, chh = cdiv(p->ny, Cfg<T>::TYMAX) * Cfg<T>::TYMAX + 5;   // corners, padded
+  k_setup_corners<T><<<(unsigned)(((long long)cw * chh + 255) / 256), 256, 0, s>>>(Dd, cw, chh);
   k_setup_cells<T><<<cdiv(p->nx * p->ny, 256), 256, 0, s>>>(Dd);
   setup_chunks<T>(D, Dd, s);
   if (D.n_waves > 0) k_setup_waves<T><<<1, 64, 0, s>>>(Dd, p->B);
