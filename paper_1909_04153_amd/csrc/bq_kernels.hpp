@@ -1333,13 +1333,15 @@ struct alignas(16) RhsSmem {
 // with the spatial operator of the predicted level (slot of level n+1, w[2])
 // and the F*, G* terms as their change F*(P*) - F*(P^n); domains without the
 // corrector are skipped.
-template <typename T, int TY, int MX, bool CORR>
-__global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
+//
+// THREADS: NT, or more in launches of few tiles (rhs_threads in the host code).
+template <typename T, int TY, int MX, bool CORR, int THREADS = NT>
+__global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
                                            int nd, int swizzle) {
   using S = RhsSmem<T, TY, MX>;
   constexpr int WX = S::WX, LW = S::LW, AXP = S::AXP, CXN = S::CXN, CP = S::CP, PW = S::PW, TXP = S::TXP;
-  constexpr int CPT = (TX * TY) / NT;                 // cells per thread
-  static_assert((TX * TY) % NT == 0, "tile must be a multiple of the block");
+  constexpr int CPT = (TX * TY) / THREADS;                 // cells per thread
+  static_assert((TX * TY) % THREADS == 0, "tile must be a multiple of the block");
   using V = Vec<T, CPT>;
   using V2 = Vec<T, 2>;
   __shared__ S sm;
@@ -1368,7 +1370,7 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
   // Cells of a thread in the per-cell phases: row vr, columns vc .. vc+CPT-1
   // (consecutive columns: one vector access per field, and the x-face pass
   // below takes the same cells, so its results stay in registers).
-  static_assert((TX / CPT) * TY == NT, "one row segment per thread");
+  static_assert((TX / CPT) * TY == THREADS, "one row segment per thread");
   int vr, vc;
   cell_of<T, CPT>(tid, vr, vc);
   const unsigned oI = (unsigned)((j0 + vr) * ipitch + i0 + vc);          // interior fields
@@ -1382,9 +1384,9 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
   // constant; repeated rows keep every round branch-free).  The workspace
   // pads every field to whole tiles plus the halo, so no index is clamped to
   // the domain: values outside it only reach cells outside it.
-  using SW = PairStaging<WX / 2, S::WY>;            // radius-2 rows
-  using SB = PairStaging<WX / 2, S::BY>;            // radius-1 rows, radius-2 columns
-  using SC = PairStaging<(CXN + 1) / 2, S::CYN>;    // corner rows
+  using SW = PairStaging<WX / 2, S::WY, THREADS>;            // radius-2 rows
+  using SB = PairStaging<WX / 2, S::BY, THREADS>;            // radius-1 rows, radius-2 columns
+  using SC = PairStaging<(CXN + 1) / 2, S::CYN, THREADS>;    // corner rows
   constexpr int KW = SW::K, KB = SB::K, KC = SC::K;
   const int cP = SW::col(tid), cC = SC::col(tid);
   auto rowW = [&](int k) { return SW::row(tid, k); };
@@ -1737,7 +1739,7 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
   constexpr int NCX = TX / MX;                  // x-chunks per tile row
   constexpr int PX = MX / 8;                    // lanes per x-chunk
   static_assert(TX % MX == 0, "chunks must tile the tile width");
-  static_assert(PX * TY * NCX <= NT - 2 * TX, "x- and y-chunk solver groups must fit the block");
+  static_assert(PX * TY * NCX <= THREADS - 2 * TX, "x- and y-chunk solver groups must fit the block");
   const bool wave_w = west_driven(D.bc[0]);
   if (tid < PX * TY * NCX) {
     const int qq = tid / PX, part = tid - qq * PX;
@@ -1768,8 +1770,8 @@ __global__ void __launch_bounds__(NT) k_rhs(const DomDev<T>* __restrict__ doms, 
       if (part == 0) chx[(size_t)cgl * ny + j] = xs[0];
       if (k0 + mh == m && mh > 0) chx[((size_t)D.cx + cgl) * ny + j] = xlast;
     }
-  } else if (tid >= NT - 2 * TX) {
-    const int c = ycol_of<T, TY>((tid - (NT - 2 * TX)) >> 1);
+  } else if (tid >= THREADS - 2 * TX) {
+    const int c = ycol_of<T, TY>((tid - (THREADS - 2 * TX)) >> 1);
     const int part = tid & 1;
     const int i = i0 + c;
     if (i < nx && j0 < ny) {
@@ -2093,12 +2095,12 @@ struct alignas(16) FinSmem {
 // corrector.  MODE 1: the same where some do; for those it finalizes the
 // predicted level (surface in w[2], no sponge, no run-up record).  MODE 2:
 // finalizes the corrector of the domains that run it.
-template <typename T, int TY, int MX, int MODE>
-__global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
+template <typename T, int TY, int MX, int MODE, int THREADS = NT>
+__global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
                                              int nd, int swizzle) {
   using S = FinSmem<T, TY, MX>;
   constexpr int CP = S::CP, BX = S::BX, BXP = S::BXP, TXP = S::TXP;
-  constexpr int CPT = (TX * TY) / NT;
+  constexpr int CPT = (TX * TY) / THREADS;
   using V = Vec<T, CPT>;
   using V2 = Vec<T, 2>;
   __shared__ S sm;
@@ -2132,7 +2134,7 @@ __global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms
   // local solutions and the new surface.
   const double dt = uni(st->dt);
   constexpr int NCX = TX / MX;
-  using SC = PairStaging<CP / 2, S::CYN>;           // corner rows
+  using SC = PairStaging<CP / 2, S::CYN, THREADS>;           // corner rows
   constexpr int KC = SC::K;
   const int cC = SC::col(tid);
   auto rowC = [&](int k) { return SC::row(tid, k); };
@@ -2150,7 +2152,7 @@ __global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms
   // y-chunks (tile columns) in the last 2 TX; every thread loads the end
   // values of both, at clamped indices, and uses one
   constexpr int PX = MX / 8;
-  static_assert(PX * TY * NCX <= NT - 2 * TX, "x- and y-chunk solver groups must fit the block");
+  static_assert(PX * TY * NCX <= THREADS - 2 * TX, "x- and y-chunk solver groups must fit the block");
   T xl, xr;
   {
     const int qx = min(tid / PX, TY * NCX - 1);
@@ -2180,7 +2182,7 @@ __global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms
     sm.u.dc[rowC(k) * CP + cC + 1] = rc[k].v[1];
   }
   __syncthreads();
-  for (int e = tid; e < S::BY * BX; e += NT) {
+  for (int e = tid; e < S::BY * BX; e += THREADS) {
     const int r = e / BX, c = e - r * BX;
     // cell (i0 - 1 + c, j0 - 1 + r): corners c + 1, c + 2 of the staged rows
     sm.db[r * BXP + c] = dbar4(sm.u.dc[r * CP + c + 1], sm.u.dc[r * CP + c + 2], sm.u.dc[(r + 1) * CP + c + 1],
@@ -2216,8 +2218,8 @@ __global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms
       for (int u = 0; u < 8; ++u)
         if (u < mh) out[u] = xs[u];
     }
-  } else if (tid >= NT - 2 * TX) {
-    const int c = ycol_of<T, TY>((tid - (NT - 2 * TX)) >> 1);
+  } else if (tid >= THREADS - 2 * TX) {
+    const int c = ycol_of<T, TY>((tid - (THREADS - 2 * TX)) >> 1);
     const int part = tid & 1;
     const int i = i0 + c;
     if (i < nx && j0 < ny) {
@@ -2307,13 +2309,13 @@ __global__ void __launch_bounds__(NT) k_final(const DomDev<T>* __restrict__ doms
   // block max -> one word per tile (max commutes with the widening to FP64,
   // so the FP32 maximum converts to the same value); no atomics, so a large
   // domain's blocks do not serialise on one address
-  __shared__ T red[NT / 64];
+  __shared__ T red[THREADS / 64];
   for (int o = 32; o > 0; o >>= 1) smax = fmax(smax, __shfl_xor(smax, o, 64));
   if ((tid & 63) == 0) red[tid >> 6] = smax;
   __syncthreads();
   if (tid == 0) {
     T m = red[0];
-    for (int k = 1; k < NT / 64; ++k) m = fmax(m, red[k]);
+    for (int k = 1; k < THREADS / 64; ++k) m = fmax(m, red[k]);
     gbl(D.smax_tile)[tile] = (double)m;               // reduced by the next step's k_dt
   }
 }

@@ -8,7 +8,7 @@
 namespace bqk {
 
 constexpr int TX = 64;      // tile width (cells)
-constexpr int NT = 256;     // threads per tile block
+constexpr int NT = 256;     // threads per tile block (more where a launch has few tiles)
 
 // Row pitches (words, mod 32) of the LDS tile buffers that the layouts
 // below assume: the radius-2 tiles and the finalize kernel's depth tile 5,
@@ -66,15 +66,15 @@ constexpr int ycol_of(int g) {
 }
 
 // Staging of an LDS tile of NR rows by 2 NPR columns in pairs of cells by
-// the NT threads of a block: thread t loads the pair of columns col(t) =
+// the THREADS threads of a block: thread t loads the pair of columns col(t) =
 // 2 (t mod NPR) of rows row(t, k) = r0(t) + RG k, k = 0 .. K - 1, with RG =
-// NT / NPR whole rows per round.  Threads past the last whole row repeat
+// THREADS / NPR whole rows per round.  Threads past the last whole row repeat
 // row RG - 1, and rows past the tile repeat its last row, so every round is
 // branch-free (the repeats store the same values again); owns(t, k) marks
 // the one thread of each cell, for the passes that update a cell in place.
-template <int NPR, int NR>
+template <int NPR, int NR, int THREADS = NT>
 struct PairStaging {
-  static constexpr int RG = NT / NPR, K = (NR + RG - 1) / RG;
+  static constexpr int RG = THREADS / NPR, K = (NR + RG - 1) / RG;
   static_assert(RG >= 1, "a row of pairs must fit the block");
   static constexpr int r0(int t) { return t / NPR < RG - 1 ? t / NPR : RG - 1; }
   static constexpr int col(int t) { return 2 * (t - (t / NPR) * NPR); }

@@ -912,6 +912,36 @@ static void launch_reduced(const Launch& L, hipStream_t s, int pass) {
   k_reduced<T><<<L.lblocks, RED_THREADS, 0, s>>>((const DomDev<T>*)L.table, L.line_map, L.nd, pass);
 }
 
+// Threads of a tile's block.  With few tiles a compute unit holds one block
+// and each of its SIMDs one wave, whose own latency is then the kernel's
+// time: fewer cells per thread and more waves shorten it, until the blocks
+// fill the chip (256 compute units, four FP32 or three FP64 blocks each) and
+// the faces and reconstructions that neighbouring threads repeat count.  The
+// arithmetic of a cell is the same for every width, bit for bit.
+// Microseconds per step, stencil kernel with 256 / 512 threads: FP32 151^2
+// 29.7 / 27.9, 1024 x 480 (480 tiles) 33.0 / 32.4, 1500 x 500 (768) 41.8 /
+// 41.4, 1024^2 (1024) 45.2 / 47.0; FP64 333 x 217 (168) 28.1 / 27.4, 1024 x
+// 256 (512) 35.6 / 35.6, 1200 x 250 (608) 42.4 / 43.8.  Finalize kernel with
+// 256 / 512 / 1024: FP32 151^2 27.9 / 25.8 / 24.9, 1024 x 256 (256) 27.6 /
+// 26.5 / 26.3, 1500 x 500 41.4 / 41.5 / 44.2.
+constexpr int rhs_threads(int tiles, int cells, int word) {
+  return cells >= 512 && tiles <= (word == 4 ? 768 : 256) ? 512 : NT;
+}
+constexpr int final_threads(int tiles, int cells, int word) {
+  return cells >= 1024 && tiles <= 256 ? 1024 : rhs_threads(tiles, cells, word);
+}
+// f(IC<n>) for n threads of a tile of CELLS cells
+template <int CELLS, typename F>
+static void threads_dispatch(int n, F&& f) {
+  if constexpr (CELLS >= 1024) {
+    if (n == 1024) return f(IC<1024>{});
+  }
+  if constexpr (CELLS >= 512) {
+    if (n == 512) return f(IC<512>{});
+  }
+  f(IC<NT>{});
+}
+
 // the stencil/update kernel (pass 0: AB3 step, 1: corrector) and the
 // finalize kernel (mode as in k_final) in the launch's tile shape
 template <typename T>
@@ -919,8 +949,13 @@ static void launch_rhs(const Launch& L, hipStream_t s, int pass) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
-    if (pass == 0) k_rhs<T, TY, MX, false><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
-    else k_rhs<T, TY, MX, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+    threads_dispatch<TX * TY>(rhs_threads(L.tiles, TX * TY, sizeof(T)), [&](auto threads) {
+      constexpr int N = decltype(threads)::value;
+      if constexpr (N <= 512) {
+        if (pass == 0) k_rhs<T, TY, MX, false, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        else k_rhs<T, TY, MX, true, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+      }
+    });
   });
 }
 
@@ -929,9 +964,12 @@ static void launch_final(const Launch& L, hipStream_t s, int mode) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
-    if (mode == 0) k_final<T, TY, MX, 0><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
-    else if (mode == 1) k_final<T, TY, MX, 1><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
-    else k_final<T, TY, MX, 2><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+    threads_dispatch<TX * TY>(final_threads(L.tiles, TX * TY, sizeof(T)), [&](auto threads) {
+      constexpr int N = decltype(threads)::value;
+      if (mode == 0) k_final<T, TY, MX, 0, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+      else if (mode == 1) k_final<T, TY, MX, 1, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+      else k_final<T, TY, MX, 2, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+    });
   });
 }
 
