@@ -201,7 +201,9 @@ __global__ void k_setup_spikes(const DomDev<T>* Dp, int dir) {
   rs[3 * CL + o] = r[m - 1];
 }
 
-// static coefficients of the interface recurrence (see k_reduced)
+// static coefficients of the interface recurrence (see k_reduced): one thread
+// per line, serial in the chunks; the spikes of 8 chunks are loaded ahead of
+// their steps
 template <typename T>
 __global__ void k_setup_reduced(const DomDev<T>* Dp, int dir) {
   const DomDev<T>& D = *Dp;
@@ -212,35 +214,65 @@ __global__ void k_setup_reduced(const DomDev<T>* Dp, int dir) {
   T* rs = dir == 0 ? D.rsx : D.rsy;
   const size_t CL = (size_t)C * L;
   T gprev = T(0);
-  for (int c = 0; c < C; ++c) {
-    const size_t o = (size_t)c * L + line;
-    const T vs = rs[o], ve = rs[CL + o], ws = rs[2 * CL + o], we = rs[3 * CL + o];
-    const T kap = T(1) / (T(1) - vs * gprev);
-    const T tau = kap * ws;
-    const T gam = ve * gprev * tau + we;
-    rs[o] = kap;
-    rs[CL + o] = kap * vs;
-    rs[2 * CL + o] = ve;
-    rs[3 * CL + o] = ve * gprev;
-    rs[4 * CL + o] = tau;
-    rs[5 * CL + o] = gam;
-    gprev = gam;
+  constexpr int RB = 8;
+  for (int c0 = 0; c0 < C; c0 += RB) {
+    T v0[RB], v1[RB], w0[RB], w1[RB];
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      const size_t o = (size_t)min(c0 + k, C - 1) * L + line;
+      v0[k] = rs[o];
+      v1[k] = rs[CL + o];
+      w0[k] = rs[2 * CL + o];
+      w1[k] = rs[3 * CL + o];
+    }
+#pragma unroll
+    for (int k = 0; k < RB; ++k) {
+      if (c0 + k >= C) break;
+      const size_t o = (size_t)(c0 + k) * L + line;
+      const T vs = v0[k], ve = v1[k], ws = w0[k], we = w1[k];
+      const T kap = T(1) / (T(1) - vs * gprev);
+      const T tau = kap * ws;
+      const T gam = ve * gprev * tau + we;
+      rs[o] = kap;
+      rs[CL + o] = kap * vs;
+      rs[2 * CL + o] = ve;
+      rs[3 * CL + o] = ve * gprev;
+      rs[4 * CL + o] = tau;
+      rs[5 * CL + o] = gam;
+      gprev = gam;
+    }
   }
 }
 
 // wave numbers of the wavemaker components: the linear dispersion relation of
 // Eq. (1)-(3) on a flat bed is a quadratic in k^2,
 //   g B d^3 K^2 + (g d - w^2 (B + 1/3) d^2) K - w^2 = 0,  K = k^2,
-// with exactly one positive root; d = mean still-water depth of column 0.
+// with exactly one positive root; d = mean still-water depth of column 0,
+// summed in row order by one thread (the column comes to LDS by the whole
+// block, which is what took the time: 514 -> 21 us for 2048 rows and 64
+// components); a thread per component.
 template <typename T>
-__global__ void k_setup_waves(const DomDev<T>* Dp, double B) {
+__global__ void __launch_bounds__(256) k_setup_waves(const DomDev<T>* Dp, double B) {
   const DomDev<T>& D = *Dp;
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+  constexpr int CH = 2048;
+  __shared__ double col[CH];
+  __shared__ double mean;
   double dsum = 0.0;
-  for (int j = 0; j < D.ny; ++j) dsum += (double)dpos(D.Dbar[(size_t)j * D.ipitch]);
-  const double d = dsum / D.ny;
+  for (int j0 = 0; j0 < D.ny; j0 += CH) {
+    const int n = min(CH, D.ny - j0);
+    for (int j = threadIdx.x; j < n; j += 256) col[j] = (double)dpos(D.Dbar[(size_t)(j0 + j) * D.ipitch]);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) dsum += col[j];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) mean = dsum / D.ny;
+  __syncthreads();
+  const double d = mean;
   const int nw = D.n_waves;
-  for (int m = 0; m < nw; ++m) {
+  for (int m = threadIdx.x; m < nw; m += 256) {
     const double om = D.wave[nw + m];
     double k = 0.0;
     if (d > 0.0 && om > 0.0) {
@@ -280,13 +312,26 @@ __global__ void k_scatter(const DomDev<T>* Dp, int which, int* bad) {
   }
 }
 
-// ghosts of level 0 at t = 0 and the CFL maximum of the initial state
+// lake at rest in level 0 (its other values are zero): k_scatter of eta = 0
+template <typename T>
+__global__ void k_rest(const DomDev<T>* Dp) {
+  const DomDev<T>& D = *Dp;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= D.nx * D.ny) return;
+  const int i = e % D.nx, j = e / D.nx;
+  const double Db = (double)D.Dbar[(size_t)j * D.ipitch + i];
+  D.w[0][(size_t)(j + 2) * D.pitch + D.xoff + i] = (T)((Db > 0.0 ? Db : 0.0) - Db);
+}
+
+// ghosts of level 0 at t = 0 and the CFL maximum of the initial state: at
+// most INIT_BLOCKS blocks, and those that find a larger maximum there leave
+// it, since atomics on one word take 50 ns each (2048^2: 248 -> 36 us)
+constexpr int INIT_BLOCKS = 1024;
 template <typename T>
 __global__ void __launch_bounds__(256) k_init_ghosts(const DomDev<T>* Dp) {
   const DomDev<T>& D = *Dp;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
   double sm = 0.0;
-  if (e < D.nx * D.ny) {
+  for (int e = blockIdx.x * 256 + threadIdx.x, n = D.nx * D.ny; e < n; e += (int)gridDim.x * 256) {
     const int i = e % D.nx, j = e / D.nx;
     const size_t g = (size_t)(j + 2) * D.pitch + D.xoff + i;
     const T wv = D.w[0][g], p = D.P[0][g], qv = D.Q[0][g];
@@ -296,7 +341,7 @@ __global__ void __launch_bounds__(256) k_init_ghosts(const DomDev<T>* Dp) {
     const T u = desing(p, h, D.eps), v = desing(qv, h, D.eps);
     const T c = sqrt(D.g * h);
     const T sx = (fabs(u) + c) / D.dx, sy = (fabs(v) + c) / D.dy;
-    sm = (sx != sx || sy != sy) ? __longlong_as_double(0x7ff0000000000000ll) : (double)fmax(sx, sy);
+    sm = fmax(sm, (sx != sx || sy != sy) ? __longlong_as_double(0x7ff0000000000000ll) : (double)fmax(sx, sy));
   }
   for (int o = 32; o > 0; o >>= 1) sm = fmax(sm, __shfl_xor(sm, o, 64));
   __shared__ double red[4];
@@ -304,7 +349,9 @@ __global__ void __launch_bounds__(256) k_init_ghosts(const DomDev<T>* Dp) {
   __syncthreads();
   if (threadIdx.x == 0) {
     const double m = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
-    atomicMax(&D.st->smax_bits, (unsigned long long)__double_as_longlong(m));
+    const unsigned long long b = (unsigned long long)__double_as_longlong(m);
+    if (b > __hip_atomic_load(&D.st->smax_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&D.st->smax_bits, b);
   }
 }
 
@@ -701,6 +748,14 @@ static void setup_chunks(const DomDev<T>& D, const DomDev<T>* Dd, hipStream_t s)
   k_setup_reduced<T><<<cdiv(D.nx, 64), 64, 0, s>>>(Dd, 1);
 }
 
+// ghosts and CFL maximum of a new level 0 of n cells
+template <typename T>
+static void init_level0(bq_domain* d, int n) {
+  const DomDev<T>* Dd = (const DomDev<T>*)d->ddev;
+  if (west_driven(desc<T>(d).bc[0])) k_init_waves<T><<<1, 64, 0, d->stream>>>(Dd);
+  k_init_ghosts<T><<<std::min(cdiv(n, 256), INIT_BLOCKS), 256, 0, d->stream>>>(Dd);
+}
+
 template <typename T>
 static int create_t(bq_domain* d, const double* depth_c) {
   const bq_params* p = &d->p;
@@ -833,7 +888,11 @@ static int create_t(bq_domain* d, const double* depth_c) {
   k_setup_corners<T><<<(unsigned)(((long long)cw * chh + 255) / 256), 256, 0, s>>>(Dd, cw, chh);
   k_setup_cells<T><<<cdiv(p->nx * p->ny, 256), 256, 0, s>>>(Dd);
   setup_chunks<T>(D, Dd, s);
-  if (D.n_waves > 0) k_setup_waves<T><<<1, 64, 0, s>>>(Dd, p->B);
+  if (D.n_waves > 0) k_setup_waves<T><<<1, 256, 0, s>>>(Dd, p->B);
+  // lake at rest
+  const int n = p->nx * p->ny;
+  k_rest<T><<<cdiv(n, 256), 256, 0, s>>>(Dd);
+  init_level0<T>(d, n);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(s));
   return BQ_OK;
@@ -858,8 +917,7 @@ static int set_state_t(bq_domain* d, const double* eta, const double* P, const d
   DevState h;
   memset(&h, 0, sizeof(h));
   HIPCHK(hipMemcpyAsync(d->st, &h, sizeof(h), hipMemcpyHostToDevice, s));
-  if (west_driven(D.bc[0])) k_init_waves<T><<<1, 64, 0, s>>>(Dd);
-  k_init_ghosts<T><<<cdiv((int)n, 256), 256, 0, s>>>(Dd);
+  init_level0<T>(d, (int)n);
   HIPCHK(hipGetLastError());
   int hflag = 0;
   HIPCHK(hipMemcpyAsync(&hflag, flag, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1667,13 +1725,6 @@ int bq_domain_create(const bq_params* p, const double* depth_c, void* dev_worksp
   d->nx = p->nx;
   d->ny = p->ny;
   rc = DISPATCH(d->precision, create_t, d, depth_c);
-  if (rc) {
-    delete d;
-    return rc;
-  }
-  // lake at rest
-  std::vector<double> z((size_t)p->nx * p->ny, 0.0);
-  rc = bq_set_state(d, z.data(), z.data(), z.data());
   if (rc) {
     delete d;
     return rc;
