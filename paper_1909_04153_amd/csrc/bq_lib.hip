@@ -511,6 +511,7 @@ struct Launch {
   int* line_map = nullptr;      // per block of lines: domain << MAP_SHIFT | block
   void* status = nullptr;       // StatusRec[nd]: staging of bq_batch_status (batches)
   int nd = 0, tiles = 0, lblocks = 0;
+  int tiles_all = 0;            // tiles of all launches that run side by side (the lanes of a batch)
   int ty = 0, mx = 0;           // tile shape shared by the members
   int any_pc = 0;               // some member runs the corrector pass
   int swizzle = 1;              // XCD-aware tile order (schedule, set per batch)
@@ -866,7 +867,7 @@ static int create_t(bq_domain* d, const double* depth_c) {
   d->L.tile_map = d->L.line_map = nullptr;
   d->L.nd = 1;
   d->L.any_pc = D.corrector;
-  d->L.tiles = D.tiles_x * D.tiles_y;
+  d->L.tiles = d->L.tiles_all = D.tiles_x * D.tiles_y;
   d->L.lblocks = line_blocks(p->nx, p->ny);
   d->L.ty = sh0.ty;
   d->L.mx = sh0.mx;
@@ -954,7 +955,7 @@ static int set_shape_t(bq_domain* d, int ty, int mx) {
   HIPCHK(hipGetLastError());
   graph_del(d->L.graph);
   d->L.graph_built = 0;
-  d->L.tiles = D.tiles_x * D.tiles_y;
+  d->L.tiles = d->L.tiles_all = D.tiles_x * D.tiles_y;
   d->L.ty = ty;
   d->L.mx = mx;
   HIPCHK(hipStreamSynchronize(s));
@@ -970,7 +971,8 @@ static void launch_reduced(const Launch& L, hipStream_t s, int pass) {
   k_reduced<T><<<L.lblocks, RED_THREADS, 0, s>>>((const DomDev<T>*)L.table, L.line_map, L.nd, pass);
 }
 
-// Threads of a tile's block.  With few tiles a compute unit holds one block
+// Threads of a tile's block, by the tiles of all launches that run side by side
+// (the lanes of a batch).  With few tiles a compute unit holds one block
 // and each of its SIMDs one wave, whose own latency is then the kernel's
 // time: fewer cells per thread and more waves shorten it, until the blocks
 // fill the chip (256 compute units, four FP32 or three FP64 blocks each) and
@@ -981,7 +983,9 @@ static void launch_reduced(const Launch& L, hipStream_t s, int pass) {
 // 41.4, 1024^2 (1024) 45.2 / 47.0; FP64 333 x 217 (168) 28.1 / 27.4, 1024 x
 // 256 (512) 35.6 / 35.6, 1200 x 250 (608) 42.4 / 43.8.  Finalize kernel with
 // 256 / 512 / 1024: FP32 151^2 27.9 / 25.8 / 24.9, 1024 x 256 (256) 27.6 /
-// 26.5 / 26.3, 1500 x 500 41.4 / 41.5 / 44.2.
+// 26.5 / 26.3, 1500 x 500 41.4 / 41.5 / 44.2.  By its own lane's tiles alone,
+// a two-lane batch of 16 domains with the corrector (2 x 640 tiles) would take
+// 512 threads and 107.4 us for 101.9.
 constexpr int rhs_threads(int tiles, int cells, int word) {
   return cells >= 512 && tiles <= (word == 4 ? 768 : 256) ? 512 : NT;
 }
@@ -1007,7 +1011,7 @@ static void launch_rhs(const Launch& L, hipStream_t s, int pass) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
-    threads_dispatch<TX * TY>(rhs_threads(L.tiles, TX * TY, sizeof(T)), [&](auto threads) {
+    threads_dispatch<TX * TY>(rhs_threads(L.tiles_all, TX * TY, sizeof(T)), [&](auto threads) {
       constexpr int N = decltype(threads)::value;
       if constexpr (N <= 512) {
         if (pass == 0) k_rhs<T, TY, MX, false, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
@@ -1022,7 +1026,7 @@ static void launch_final(const Launch& L, hipStream_t s, int mode) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
-    threads_dispatch<TX * TY>(final_threads(L.tiles, TX * TY, sizeof(T)), [&](auto threads) {
+    threads_dispatch<TX * TY>(final_threads(L.tiles_all, TX * TY, sizeof(T)), [&](auto threads) {
       constexpr int N = decltype(threads)::value;
       if (mode == 0) k_final<T, TY, MX, 0, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
       else if (mode == 1) k_final<T, TY, MX, 1, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
@@ -1297,7 +1301,7 @@ static int fill_launch(Launch& L, char* m, const std::vector<bq_domain*>& doms, 
   L.line_map = (int*)(m + tb + mb);
   L.status = m + tb + mb + lb;
   L.nd = nd;
-  L.tiles = (int)tmap.size();
+  L.tiles = L.tiles_all = (int)tmap.size();
   L.lblocks = (int)lmap.size();
   L.any_pc = 0;
   for (int k = 0; k < nd; ++k) L.any_pc |= tab[k].corrector;
@@ -1385,6 +1389,7 @@ static int batch_build_t(bq_batch* b) {
       rc = fill_launch<T>(b->G[g], m + off, part[g], b->stream, stat);
       off += sg[g];
       b->G[g].swizzle = b->swizzle;
+      b->G[g].tiles_all = b->L.tiles;
     }
     if (rc) return rc;
   }
