@@ -1837,9 +1837,10 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
 // changes its results.  Against one thread per line sweeping alone (HIP
 // events around the launch): 41.6 -> 13.0 us on 2048^2 FP32, 33.3 -> 8.7 on
 // 1024 x 256 FP64, 10.7 -> 7.1 on 200 x 20 FP64; composing the segments' maps
-// in parallel, which rounds differently, would take 11.3, 8.2 and 6.7.  Lines of more than RED_SEGS * RED_MAX chunks are
-// taken in panels, from the first to the last and back, with sigma and alpha
-// of all but the last panel kept in the result's slots.
+// in parallel, which rounds differently, would take 11.3, 8.2 and 6.7.
+// Lines of more than RED_SEGS * RED_MAX chunks are taken in panels, from the
+// first to the last and back, with sigma and alpha of all but the last panel
+// kept in the result's slots.
 
 constexpr int RED_LINES = 16, RED_SEGS = 16, RED_MAX = 8;
 constexpr int RED_PANEL = RED_SEGS * RED_MAX;      // chunks of a line per panel

@@ -442,7 +442,7 @@ __global__ void __launch_bounds__(256) k_diag_part(const DomDev<T>* Dp) {
 
 // sum of the partials (fixed tree); the per-tile CFL maxima are folded into
 // the state's maximum for reporting (idempotent for the next Delta t)
-// The state goes to `host` (pinned memory) as well.
+// The state goes to `host` (pinned memory, may be NULL) as well.
 template <typename T>
 __global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp, DevState* host) {
   const DomDev<T>& D = *Dp;
@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp, DevSt
     D.st->energy = se[0] * D.dx_d * D.dy_d;
     const double s0 = __longlong_as_double((long long)D.st->smax_bits);
     D.st->smax_bits = (unsigned long long)__double_as_longlong(fmax(s0, sx[0]));
-    store_state(host, load_state(D.st));
+    if (host) store_state(host, load_state(D.st));
   }
 }
 
@@ -533,7 +533,6 @@ struct bq_domain {
   DomDev<double> dd;
   void* ddev = nullptr;         // device DomDev<T>
   DevState* st = nullptr;
-  DevState* hst = nullptr;      // pinned copy of the state (allocated by the first bq_sync that reports)
   Launch L;                     // tables in the workspace
   int graph_steps = 16;
 };
@@ -1139,6 +1138,44 @@ static int step_dt_t(bq_domain* d, double dt) {
   return BQ_OK;
 }
 
+// Pinned memory that the calls of bq_sync in progress bring states back
+// through: one page of SYNC_SLOTS states for the process, like the static
+// table array made once and kept, since releasing pinned memory waits for
+// every stream of the device (a domain that held its own was freed in 32 us,
+// one without in 4).  A slot belongs to one call; calls beyond SYNC_SLOTS at
+// once, or all where the page can't be had, take a copy to ordinary memory.
+struct SyncSlots {
+  static constexpr int SYNC_SLOTS = 64;
+  std::mutex m;
+  DevState* page = nullptr;
+  bool tried = false;
+  unsigned long long used = 0;
+
+  DevState* take() {
+    std::lock_guard<std::mutex> lock(m);
+    if (!tried) {
+      tried = true;
+      // (allocating is not part of any capture that runs elsewhere meanwhile)
+      hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+      const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+      if (hipHostMalloc((void**)&page, SYNC_SLOTS * sizeof(DevState), hipHostMallocPortable) != hipSuccess) {
+        page = nullptr;
+        (void)hipGetLastError();
+      }
+      if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    if (!page || used == ~0ull) return nullptr;
+    const int k = __builtin_ctzll(~used);
+    used |= 1ull << k;
+    return page + k;
+  }
+  void give(DevState* s) {
+    std::lock_guard<std::mutex> lock(m);
+    used &= ~(1ull << (s - page));
+  }
+};
+static SyncSlots sync_slots;
+
 template <typename T>
 static int sync_t(bq_domain* d, bq_info* out) {
   DevState h;
@@ -1146,12 +1183,18 @@ static int sync_t(bq_domain* d, bq_info* out) {
     // the sums are queued behind the steps and write the state to pinned host
     // memory, so that one wait brings everything back (a 151 x 151 domain's
     // step and sync in turn: 81.5 -> 52.7 us)
-    if (!d->hst) HIPCHK(hipHostMalloc((void**)&d->hst, sizeof(DevState), hipHostMallocDefault));
+    DevState* const slot = sync_slots.take();
     k_diag_part<T><<<NDIAG, 256, 0, d->stream>>>((const DomDev<T>*)d->ddev);
-    k_diag_final<T><<<1, NDIAG, 0, d->stream>>>((const DomDev<T>*)d->ddev, d->hst);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(d->stream));
-    h = *d->hst;
+    k_diag_final<T><<<1, NDIAG, 0, d->stream>>>((const DomDev<T>*)d->ddev, slot);
+    hipError_t e = hipGetLastError();
+    if (!slot && e == hipSuccess) e = hipMemcpyAsync(&h, d->st, sizeof(h), hipMemcpyDeviceToHost, d->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(d->stream);
+    // (on an error the slot may still be written later: it is not given back)
+    if (e != hipSuccess) return fail(BQ_EDEVICE, "bq_sync: %s", hipGetErrorString(e));
+    if (slot) {
+      h = *slot;
+      sync_slots.give(slot);
+    }
     out->t = h.t;
     out->n = h.n;
     out->dt_last = h.dt1;
@@ -1741,7 +1784,6 @@ int bq_domain_create(const bq_params* p, const double* depth_c, void* dev_worksp
 int bq_domain_free(bq_domain* d) {
   if (!d) return fail(BQ_EINVAL, "NULL domain");
   graph_del(d->L.graph);
-  if (d->hst) (void)hipHostFree(d->hst);
   delete d;
   return BQ_OK;
 }
