@@ -1069,64 +1069,90 @@ __device__ __forceinline__ void commit(DevState& st) {
   }
 }
 
+// f over the 64 lanes of a wave in the order of a butterfly (32, 16, ... 1
+// lanes apart; f commutes), every lane with the result.  Row swaps and DPP
+// instead of shuffles, which take an LDS trip per word and level.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+}
+template <typename F>
+__device__ __forceinline__ double wave_fold(double v, F f) {
+  const auto both = [](auto lo, auto hi, int k) { return __hiloint2double((int)hi[k], (int)lo[k]); };
+  {
+    const unsigned l = (unsigned)__double2loint(v), h = (unsigned)__double2hiint(v);
+    const auto lo = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    v = f(both(lo, hi, 0), both(lo, hi, 1));
+  }
+  {
+    const unsigned l = (unsigned)__double2loint(v), h = (unsigned)__double2hiint(v);
+    const auto lo = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+    v = f(both(lo, hi, 0), both(lo, hi, 1));
+  }
+  v = f(v, dpp<0x128>(v));   // row_ror:8
+  v = f(v, dpp<0x124>(v));   // row_ror:4, of a row that repeats after 8 lanes
+  v = f(v, dpp<0x4e>(v));    // quad_perm 2 3 0 1
+  return f(v, dpp<0xb1>(v)); // quad_perm 1 0 3 2
+}
+
+// one component of the incident wave train at west ghost column c = 0, 1 (its
+// centre is at x = -(c + 1/2) dx)
+struct WestTerm {
+  double amp, om, ph, ck, hk;     // ck = om / k, hk = (c + 1/2) k
+};
 template <typename T>
-__device__ void west_ghosts(const DomDev<T>& D, double t, double* gw, double* gP) {
-  // surface and flux prescribed at the centres of west ghost cells -1 and -2
-  // (x = -dx/2, -3dx/2) at time t; only thread 0's result is used
-  const int tid = threadIdx.x;
-  const double r = D.wave_ramp > 0.0 ? 1.0 - exp(-(t / D.wave_ramp) * (t / D.wave_ramp)) : 1.0;
-  if (D.bc[0] == TIMESERIES) {
-    // samples interpolated linearly in time, held outside their span; the
-    // same values in both ghost columns
-    if (tid == 0) {
-      const int n = D.ts_n;
-      const double* se = D.wave;
-      const double* sp = D.wave + n;
-      const double s = t / D.ts_dt;
-      double e, p;
-      if (!(s > 0.0)) {
-        e = se[0];
-        p = sp[0];
-      } else if (s >= (double)(n - 1)) {
-        e = se[n - 1];
-        p = sp[n - 1];
-      } else {
-        const int k = (int)s;
-        const double f = s - (double)k;
-        e = se[k] + f * (se[k + 1] - se[k]);
-        p = sp[k] + f * (sp[k + 1] - sp[k]);
-      }
-      gw[0] = gw[1] = r * e;
-      gP[0] = gP[1] = r * p;
-    }
-    return;
-  }
-  // incident wave train: sum of the components
-  double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
+__device__ __forceinline__ WestTerm west_term(const DomDev<T>& D, int m, int c) {
   const int nw = D.n_waves;
-  for (int m = tid; tid < 64 && m < nw; m += 64) {
-    const double amp = D.wave[m], om = D.wave[nw + m], ph = D.wave[2 * nw + m], k = D.wave[3 * nw + m];
-    const double s1 = r * amp * sin(om * t + 0.5 * k * D.dx_d + ph);
-    const double s2 = r * amp * sin(om * t + 1.5 * k * D.dx_d + ph);
-    a0 += s1;
-    a1 += om / k * s1;
-    a2 += s2;
-    a3 += om / k * s2;
+  const double k = D.wave[3 * nw + m], om = D.wave[nw + m];
+  return {D.wave[m], om, D.wave[2 * nw + m], om / k, (c == 0 ? 0.5 : 1.5) * k};
+}
+__device__ __forceinline__ double west_ramp(double ramp, double t) {
+  return ramp > 0.0 ? 1.0 - exp(-(t / ramp) * (t / ramp)) : 1.0;
+}
+// surface and flux that the wave train prescribes in ghost column c at time t,
+// summed by one wave; w is its lanes' first component
+template <typename T>
+__device__ __forceinline__ void west_train(const DomDev<T>& D, double t, int c, WestTerm w, double& gw, double& gP) {
+  const int lane = threadIdx.x & 63, nw = D.n_waves;
+  const double r = west_ramp(D.wave_ramp, t);
+  double a = 0, b = 0;
+  for (int m = lane; m < nw; m += 64) {
+    if (m != lane) w = west_term(D, m, c);
+    const double s = r * w.amp * sin(fma_(w.hk, D.dx_d, w.om * t) + w.ph);
+    a += s;
+    b += w.ck * s;
   }
-  // the first wave sums its lanes' partial sums by a butterfly (lanes past
-  // the component count hold zeros)
-  if (tid < 64) {
-    for (int o = 32; o > 0; o >>= 1) {
-      a0 += __shfl_xor(a0, o, 64);
-      a1 += __shfl_xor(a1, o, 64);
-      a2 += __shfl_xor(a2, o, 64);
-      a3 += __shfl_xor(a3, o, 64);
-    }
-    if (tid == 0) {
-      gw[0] = a0; gP[0] = a1; gw[1] = a2; gP[1] = a3;
-    }
+  const auto add = [](double x, double y) { return x + y; };
+  gw = wave_fold(a, add);
+  gP = wave_fold(b, add);
+}
+// a boundary series' values at time t: samples interpolated linearly in time,
+// held outside their span; the same values in both ghost columns
+template <typename T>
+__device__ __forceinline__ void west_series(const DomDev<T>& D, double t, double& gw, double& gP) {
+  const int n = D.ts_n;
+  const double* se = D.wave;
+  const double* sp = D.wave + n;
+  const double s = t / D.ts_dt, r = west_ramp(D.wave_ramp, t);
+  double e, p;
+  if (!(s > 0.0)) {
+    e = se[0];
+    p = sp[0];
+  } else if (s >= (double)(n - 1)) {
+    e = se[n - 1];
+    p = sp[n - 1];
+  } else {
+    const int k = (int)s;
+    const double f = s - (double)k;
+    e = se[k] + f * (se[k + 1] - se[k]);
+    p = sp[k] + f * (sp[k + 1] - sp[k]);
   }
-  __syncthreads();
+  gw = r * e;
+  gP = r * p;
 }
 
 // one block of DT_THREADS per domain
@@ -1147,6 +1173,15 @@ __global__ void __launch_bounds__(DT_THREADS) k_dt(const DomDev<T>* __restrict__
   const int fixed_dt = D.fixed_dt, fstar_order = D.fstar_order, corrector = D.corrector;
   __asm__ volatile("" ::"s"(t_end), "s"(cfl), "s"(ema), "s"(dt_init), "s"(dt_max), "s"(dt_min), "s"(fixed_dt),
                    "s"(fstar_order), "s"(corrector));
+  // the wave train's components too, the waves 1 and 2 for a ghost column
+  // each: what does not depend on the new time is formed while one thread
+  // of wave 0 decides the step.  This kernel is latency alone: with both
+  // columns in wave 0, loaded after the decision, a step took 35.4 us on 1024
+  // x 256 FP64 for 34.9, 26.5 for 25.8 in FP32, 27.0 for 26.3 on 333 x 217
+  const int bc0 = D.bc[0], nw = D.n_waves, lane = threadIdx.x & 63, col = uni((int)(threadIdx.x >> 6)) - 1;
+  const bool train = (bc0 == SINE || bc0 == IRREGULAR) && (col == 0 || col == 1);
+  WestTerm wt = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if (train && lane < nw) wt = west_term(D, lane, col);
   // CFL maximum of the current state: the finalize kernel's per-tile maxima
   // (a NaN there is already +inf) and the initial state's value
   double tmax = 0.0;
@@ -1167,7 +1202,7 @@ __global__ void __launch_bounds__(DT_THREADS) k_dt(const DomDev<T>* __restrict__
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) tmax = fmax(tmax, tm[u]);
-    for (int o = 32; o > 0; o >>= 1) tmax = fmax(tmax, __shfl_xor(tmax, o, 64));
+    tmax = wave_fold(tmax, [](double x, double y) { return fmax(x, y); });
     __shared__ double wmax[DT_THREADS / 64];
     if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = tmax;
     __syncthreads();
@@ -1269,12 +1304,18 @@ __global__ void __launch_bounds__(DT_THREADS) k_dt(const DomDev<T>* __restrict__
     store_state(st, S);
   }
   __syncthreads();
-  if (go && west_driven(D.bc[0])) {
-    double gw[2], gP[2];
-    west_ghosts(D, tn, gw, gP);
-    if (threadIdx.x == 0) {
-      st->gw[0] = gw[0]; st->gw[1] = gw[1]; st->gP[0] = gP[0]; st->gP[1] = gP[1];
+  if (!go) return;
+  double gw, gP;
+  if (train) {
+    west_train(D, tn, col, wt, gw, gP);
+    if (lane == 0) {
+      st->gw[col] = gw;
+      st->gP[col] = gP;
     }
+  } else if (bc0 == TIMESERIES && threadIdx.x == 0) {
+    west_series(D, tn, gw, gP);
+    st->gw[0] = st->gw[1] = gw;
+    st->gP[0] = st->gP[1] = gP;
   }
 }
 

@@ -355,14 +355,19 @@ __global__ void __launch_bounds__(256) k_init_ghosts(const DomDev<T>* Dp) {
   }
 }
 
-// wavemaker ghost values at t = 0 (one block)
+// wavemaker ghost values at t = 0 (one wave)
 template <typename T>
 __global__ void __launch_bounds__(64) k_init_waves(const DomDev<T>* Dp) {
   const DomDev<T>& D = *Dp;
-  double gw[2], gP[2];
-  west_ghosts(D, D.st->t, gw, gP);
-  if (threadIdx.x == 0) {
-    D.st->gw[0] = gw[0]; D.st->gw[1] = gw[1]; D.st->gP[0] = gP[0]; D.st->gP[1] = gP[1];
+  const double t = D.st->t;
+  for (int c = 0; c < 2; ++c) {
+    double gw, gP;
+    if (D.bc[0] == TIMESERIES) west_series(D, t, gw, gP);
+    else west_train(D, t, c, (int)threadIdx.x < D.n_waves ? west_term(D, threadIdx.x, c) : WestTerm{}, gw, gP);
+    if (threadIdx.x == 0) {
+      D.st->gw[c] = gw;
+      D.st->gP[c] = gP;
+    }
   }
 }
 
