@@ -446,7 +446,7 @@ __global__ void __launch_bounds__(256) k_diag_part(const DomDev<T>* Dp) {
 }
 
 // sum of the partials (fixed tree); the per-tile CFL maxima are folded into
-// the state's maximum for reporting (idempotent for the next Delta t)
+// the state's maximum for reporting (idempotent for the next Delta t).
 // The state goes to `host` (pinned memory, may be NULL) as well.
 template <typename T>
 __global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp, DevState* host) {
@@ -468,11 +468,16 @@ __global__ void __launch_bounds__(NDIAG) k_diag_final(const DomDev<T>* Dp, DevSt
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    D.st->mass = sm[0] * D.dx_d * D.dy_d;
-    D.st->energy = se[0] * D.dx_d * D.dy_d;
-    const double s0 = __longlong_as_double((long long)D.st->smax_bits);
-    D.st->smax_bits = (unsigned long long)__double_as_longlong(fmax(s0, sx[0]));
-    if (host) store_state(host, load_state(D.st));
+    // read, changed and written as a whole: load_state and store_state move
+    // the state as integer words, which the compiler may order freely against
+    // accesses to its members
+    DevState S = load_state(D.st);
+    S.mass = sm[0] * D.dx_d * D.dy_d;
+    S.energy = se[0] * D.dx_d * D.dy_d;
+    S.smax_bits =
+        (unsigned long long)__double_as_longlong(fmax(__longlong_as_double((long long)S.smax_bits), sx[0]));
+    store_state(D.st, S);
+    if (host) store_state(host, S);
   }
 }
 
