@@ -1186,8 +1186,20 @@ struct SyncSlots {
 };
 static SyncSlots sync_slots;
 
+// A call that waits for its stream can't be part of a capture: it is refused
+// before it queues anything, so that the capture holds no kernel that writes
+// to a slot given back, or to the caller's memory, when it is replayed.
+static int refuse_capture(const bq_domain* d, const char* call) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (!d->stream || hipStreamIsCapturing(d->stream, &cs) != hipSuccess || cs == hipStreamCaptureStatusNone)
+    return BQ_OK;
+  return fail(BQ_EDEVICE, "%s: the domain's stream is being captured", call);
+}
+
 template <typename T>
 static int sync_t(bq_domain* d, bq_info* out) {
+  const int rc = refuse_capture(d, "bq_sync");
+  if (rc) return rc;
   DevState h;
   if (out) {
     // the sums are queued behind the steps and write the state to pinned host
@@ -1223,6 +1235,8 @@ static int sync_t(bq_domain* d, bq_info* out) {
 
 template <typename T>
 static int read_t(bq_domain* d, int which, double* out) {
+  const int rc = refuse_capture(d, "bq_read");
+  if (rc) return rc;
   const int n = d->nx * d->ny;
   k_gather<T><<<cdiv(n, 256), 256, 0, d->stream>>>((const DomDev<T>*)d->ddev, which);
   HIPCHK(hipGetLastError());
