@@ -42,7 +42,7 @@ WORDS_STEP = 24
 # kernel sources it was taken on; it is reported only while they match
 PROFILE_SUMMARIES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = ("paper_1909_04153_amd/csrc/bq_kernels.hpp", "paper_1909_04153_amd/csrc/bq_layout.hpp",
-                  "paper_1909_04153_amd/csrc/bq_lib.hip")
+                  "paper_1909_04153_amd/csrc/bq_fp64.hpp", "paper_1909_04153_amd/csrc/bq_lib.hip")
 
 
 def kernel_source_hash():

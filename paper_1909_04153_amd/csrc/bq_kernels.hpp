@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bq_fp64.hpp"
 #include "bq_layout.hpp"
 
 namespace bqk {
@@ -229,56 +230,33 @@ __device__ __forceinline__ void stv_nt(T* base, unsigned off, const Vec<T, N>& v
   __builtin_nontemporal_store(x, (gp<R>)(b + (unsigned)(off * (unsigned)sizeof(T))));
 }
 
-// Square root, reciprocal and cube root.  FP64 uses the correctly rounded
-// operations (parity with the FP64 oracle at 1e-12); FP32 uses the hardware
-// transcendental instructions (about 1 ulp), whose error is far below the
-// FP32 path's own rounding of the state.
+// Square root, reciprocal and x^(-1/3) for any argument.  FP64: the library's
+// correctly rounded root and division, and an inverse cube root good to 1.2
+// units in the last place; FP32: the hardware's transcendental instructions
+// (about 1 ulp), whose error is far below the FP32 path's own rounding of the
+// state.
 template <typename T> __device__ __forceinline__ T fsqrt(T x);
 template <typename T> __device__ __forceinline__ T frcp(T x);
 template <typename T> __device__ __forceinline__ T frcbrt(T x);   // x^(-1/3), x > 0
 template <> __device__ __forceinline__ double fsqrt<double>(double x) { return sqrt(x); }
 template <> __device__ __forceinline__ double frcp<double>(double x) { return 1.0 / x; }
-// FP64: from the FP32 value (about 1e-6) by two steps of y += y (1 - x y^3) / 3
-// (Newton's, quadratic: 1e-12, then rounding); outside the FP32 range by the
-// library's cube root
+// FP64: from the FP32 value (4e-6); outside the FP32 range by the library's
+// cube root
 template <> __device__ __forceinline__ double frcbrt<double>(double x) {
   if (!(x > 1e-30 && x < 1e30)) return 1.0 / cbrt(x);
-  double y = (double)__builtin_amdgcn_exp2f(-0.33333333f * __builtin_amdgcn_logf((float)x));
-  y = __builtin_fma(y * (1.0 / 3.0), __builtin_fma(-x * y, y * y, 1.0), y);
-  return __builtin_fma(y * (1.0 / 3.0), __builtin_fma(-x * y, y * y, 1.0), y);
+  return rcbrt_from(x, (double)__builtin_amdgcn_exp2f(-0.33333333f * __builtin_amdgcn_logf((float)x)));
 }
 template <> __device__ __forceinline__ float fsqrt<float>(float x) { return __builtin_amdgcn_sqrtf(x); }
 template <> __device__ __forceinline__ float frcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
-// Reciprocal, square root and inverse square root of a positive number.  FP64:
-// the hardware's approximation (2^-24) refined to about 1 ulp, without the
-// scaling and the special cases of the correctly rounded operations (5, 8
-// and 8 instructions against 11, 18 and, as a division by a root, 29).
+// Reciprocal, division by a number of known reciprocal, square root and (FP64)
+// inverse square root, of a positive number in ordinary range
 __device__ __forceinline__ float rcp_n(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ float div_n(float t, float, float id) { return t * id; }
 __device__ __forceinline__ float sqrt_n(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ __forceinline__ double rcp_n(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
-}
-// one coupled step for s = sqrt(x) and h = 1 / (2 sqrt(x))
-__device__ __forceinline__ void root_step(double x, double& s, double& h) {
-  const double y = __builtin_amdgcn_rsq(x);
-  s = x * y;
-  h = 0.5 * y;
-  const double r = __builtin_fma(-h, s, 0.5);
-  s = __builtin_fma(s, r, s);
-  h = __builtin_fma(h, r, h);
-}
-__device__ __forceinline__ double sqrt_n(double x) {
-  double s, h;
-  root_step(x, s, h);
-  return __builtin_fma(__builtin_fma(-s, s, x), h, s);
-}
-__device__ __forceinline__ double half_rsq_n(double x) {   // 1 / (2 sqrt(x))
-  double s, h;
-  root_step(x, s, h);
-  return __builtin_fma(h, __builtin_fma(-h, s, 0.5), h);
-}
+__device__ __forceinline__ double rcp_n(double x) { return rcp_from(x, __builtin_amdgcn_rcp(x)); }
+__device__ __forceinline__ double div_n(double t, double d, double id) { return div_from(t, d, id); }
+__device__ __forceinline__ double sqrt_n(double x) { return sqrt_from(x, __builtin_amdgcn_rsq(x)); }
+__device__ __forceinline__ double rsq_n(double x) { return rsq_from(x, __builtin_amdgcn_rsq(x)); }
 // The hardware log takes a subnormal input as 0 (giving +inf here, and a
 // NaN once multiplied by the zero velocity of a film that thin): depths are
 // raised to the smallest normal value first, which leaves h^(-1/3) finite
@@ -432,14 +410,15 @@ __device__ __forceinline__ void side_speeds(Side<float>& s, float qn, float qt, 
   }
   s.c = sqrt_n(g * s.h);
 }
-// FP64 keeps the one expression everywhere, so that at wet/dry fronts it
-// rounds like the FP64 reference
+// FP64 keeps the one expression everywhere, u = q h / sqrt(z) with one root for
+// both velocities: four roundings after h^4 where the definition's own order,
+// sqrt(2) h q / sqrt(h^4 + max(h^4, eps)), has five
 template <bool DEEP = false>
 __device__ __forceinline__ void side_speeds(Side<double>& s, double qn, double qt, double eps, double g) {
 #pragma clang fp contract(off)
   const double h2 = s.h * s.h;
   const double h4 = h2 * h2;
-  const double vf = 2.8284271247461901 * s.h * half_rsq_n(h4 + (DEEP ? h4 : fmax(h4, eps)));
+  const double vf = s.h * rsq_n(DEEP ? h4 : desing_sq(h4, eps));
   s.un = qn * vf;
   s.ut = qt * vf;
   s.qn = s.h * s.un;
@@ -825,7 +804,7 @@ __device__ __forceinline__ void group_solve_(const T* Dl, int ds, int m, const T
     T t = rv[e];
 #pragma unroll
     for (int f = e + 1; f < N; ++f) t -= M[e][f] * z[f];
-    z[e] = t * id[e];
+    z[e] = div_n(t, M[e][e], id[e]);
   }
   T Rp = T(0), Lm = T(0);                      // R_part, L_{part-1}
 #pragma unroll
@@ -984,7 +963,7 @@ __device__ __forceinline__ void group_response_(const T* Dl, int ds, int m, cons
     T t = rv[e];
 #pragma unroll
     for (int q = e + 1; q < N; ++q) t -= M[e][q] * z[q];
-    z[e] = t * id[e];
+    z[e] = div_n(t, M[e][e], id[e]);
   }
   T Rp = T(0), Lm = T(0);
 #pragma unroll
