@@ -189,7 +189,9 @@ int bq_step(bq_domain* d, int32_t n_steps);
 int bq_step_dt(bq_domain* d, double dt);
 
 /* Wait for the domain's stream; fill *out (may be NULL) and return the
- * latched status. */
+ * latched status.  *out comes back through one page of pinned host memory,
+ * which the first such call of the process allocates.  Refused with
+ * BQ_EDEVICE while the stream is being captured, as bq_read is. */
 int bq_sync(bq_domain* d, bq_info* out);
 
 /* Synchronous read of the interior, FP64: which = 0 eta, 1 P, 2 Q, 3 w,

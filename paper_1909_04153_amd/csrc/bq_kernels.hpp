@@ -1852,15 +1852,18 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
 // bytes at most): one trip to memory and the chain itself, three dependent
 // operations per chunk forward and one backward.  16 lines to a block spread
 // the lines thinly (a 2048^2 domain gives 256 blocks, one per compute unit,
-// one of 200 x 20 cells 15).  The sweep keeps the order and the rounding of
-// the plain recurrence, so neither the launch nor the batch around a domain
-// changes its results.  Against one thread per line sweeping alone (HIP
-// events around the launch): 41.6 -> 13.0 us on 2048^2 FP32, 33.3 -> 8.7 on
-// 1024 x 256 FP64, 10.7 -> 7.1 on 200 x 20 FP64; composing the segments' maps
-// in parallel, which rounds differently, would take 11.3, 8.2 and 6.7.
+// one of 200 x 20 cells 15).  The sweep takes the chunks in their order and
+// rounds each as one thread sweeping alone in groups of 8 chunks did, so
+// neither the launch nor the batch around a domain changes its results.
+// Against that one thread per line (HIP events around the launch): 41.6 ->
+// 12.6 us on 2048^2 FP32, 33.3 -> 8.7 on 1024 x 256 FP64, 10.7 -> 7.3 on 200 x
+// 20 FP64; composing the segments' maps in parallel, which rounds differently,
+// would take 11.3, 8.2 and 6.7.
 // Lines of more than RED_SEGS * RED_MAX chunks are taken in panels, from the
 // first to the last and back, with sigma and alpha of all but the last panel
-// kept in the result's slots.
+// kept in the result's slots: 64 columns of FP64 rows take 11.4 us with 128
+// chunks (33.0 by one thread per line), 14.5 with 129 (40.4), 79 with 1024
+// (250).
 
 constexpr int RED_LINES = 16, RED_SEGS = 16, RED_MAX = 8;
 constexpr int RED_PANEL = RED_SEGS * RED_MAX;      // chunks of a line per panel
@@ -1952,7 +1955,10 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduced(const DomDev<T>* __rest
           if (decltype(r)::value == row) {
 #pragma unroll
             for (int k = 0; k < RED_MAX; ++k) {
-              // (which of the two products is rounded first is part of the result)
+              // Which of the two products is rounded by itself is part of the
+              // FP32 results: in the first chunk of a thread the other one, as the
+              // former sweep's groups of 8 chunks came out of the compiler.
+              // (RED_MAX is that 8: another value would round differently.)
               sg[k] = k == 0 ? fma_(k2[k], a, k1[k] * xs[k]) : fma_(k1[k], xs[k], k2[k] * a);
               a = fma_(m2[k], sg[k], fma_(m1[k], a, xe[k]));
               al[k] = a;

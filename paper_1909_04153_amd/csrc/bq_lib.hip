@@ -995,6 +995,13 @@ static void launch_reduced(const Launch& L, hipStream_t s, int pass) {
 // 26.5 / 26.3, 1500 x 500 41.4 / 41.5 / 44.2.  By its own lane's tiles alone,
 // a two-lane batch of 16 domains with the corrector (2 x 640 tiles) would take
 // 512 threads and 107.4 us for 101.9.
+// Domains stepped side by side on streams of their own don't see each other,
+// and together they can fill the chip that the rule took for empty: it is set
+// for a domain that runs alone or in a batch.  Microseconds for a step of each
+// of 1 / 2 / 4 / 8 such domains by the rule, and with 256 threads: FP32 400^2
+// 25 / 32 / 60 / 80, 29 / 34 / 66 / 82; 1024 x 256 26 / 34 / 50 / 94, 29 / 35 /
+// 46 / 87; 1500 x 500 41 / 57 / 94 / 186, 42 / 55 / 85 / 164; FP64 1024 x 128
+// (256 tiles) 28 / 36 / 73 / 121, 28 / 36 / 70 / 116.
 constexpr int rhs_threads(int tiles, int cells, int word) {
   return cells >= 512 && tiles <= (word == 4 ? 768 : 256) ? 512 : NT;
 }
@@ -1204,7 +1211,7 @@ static int sync_t(bq_domain* d, bq_info* out) {
   if (out) {
     // the sums are queued behind the steps and write the state to pinned host
     // memory, so that one wait brings everything back (a 151 x 151 domain's
-    // step and sync in turn: 81.5 -> 52.7 us)
+    // step and sync in turn: 81 -> 45 us)
     DevState* const slot = sync_slots.take();
     k_diag_part<T><<<NDIAG, 256, 0, d->stream>>>((const DomDev<T>*)d->ddev);
     k_diag_final<T><<<1, NDIAG, 0, d->stream>>>((const DomDev<T>*)d->ddev, slot);
