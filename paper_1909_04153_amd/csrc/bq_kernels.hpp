@@ -149,8 +149,9 @@ __device__ __forceinline__ void pin(T& v) {
 }
 
 // Element `off` of a field whose base address is the same for the whole
-// block: a scalar base plus a 32-bit per-lane byte offset (the workspace
-// keeps every field below 4 GiB).
+// block: a scalar base plus a 32-bit per-lane byte offset (below 4 GiB: the
+// tile kernels have a form for larger fields, and the line solves' arrays are
+// below by the limit on a domain's padded fields).
 template <typename T>
 __device__ __forceinline__ T ldu(const T* base, unsigned off) {
   const gp<const char> b = (gp<const char>)(const char*)base;
@@ -1355,7 +1356,12 @@ struct alignas(16) RhsSmem {
 // corrector are skipped.
 //
 // THREADS: NT, or more in launches of few tiles (rhs_threads in the host code).
-template <typename T, int TY, int MX, bool CORR, int THREADS = NT>
+// BIG: some field of the domain exceeds 4 GiB, the reach of a lane's byte
+// offset (ldu, ldv), so that every field is addressed from the tile's corner.
+// The 60 scalar additions this takes cost 1 to 2 % of a step (333 x 217 FP64
+// 5590 -> 5696 us for 200, 2048^2 FP32 80.0 -> 81.3 ms for 600): the launches
+// of smaller fields go without.
+template <typename T, int TY, int MX, bool CORR, int THREADS = NT, bool BIG = false>
 __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
                                            int nd, int swizzle) {
   using S = RhsSmem<T, TY, MX>;
@@ -1393,8 +1399,14 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
   static_assert((TX / CPT) * TY == THREADS, "one row segment per thread");
   int vr, vc;
   cell_of<T, CPT>(tid, vr, vc);
-  const unsigned oI = (unsigned)((j0 + vr) * ipitch + i0 + vc);          // interior fields
-  const unsigned oG = (unsigned)((j0 + vr + 2) * pitch + xoff + i0 + vc);  // ghosted fields
+  // BIG: the tile's corner in the fields, as scalars, from which the lanes
+  // count; else they count from the fields' first element
+  const int jl = BIG ? 0 : j0, il = BIG ? 0 : i0, xo = BIG ? 2 : xoff;
+  const size_t tI = BIG ? (size_t)j0 * ipitch + i0 : 0;               // interior fields: cell (i0, j0)
+  const size_t tG = BIG ? (size_t)j0 * pitch + xoff + i0 - 2 : 0;     // ghosted fields: cell (i0 - 2, j0 - 2)
+  const size_t tC = BIG ? (size_t)j0 * cpitch + i0 : 0;               // corner (i0 - 2, j0 - 2)
+  const unsigned oI = (unsigned)((jl + vr) * ipitch + il + vc);
+  const unsigned oG = (unsigned)((jl + vr + 2) * pitch + xo + il + vc);
 
   // ---- phase 0: issue every load of the tile before the first LDS store ----
   // The halo tiles are read in pairs of cells (8 or 16 bytes per lane): a
@@ -1415,24 +1427,24 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
   // the history fields' addresses first (a wait for a descriptor read
   // would also wait for every field load issued before it)
   const int l1 = CORR ? slot : s1, l2 = CORR ? s1 : s2;
-  const T* const pE1 = uni((const T*)D.E[l1]);
-  const T* const pE2 = uni((const T*)D.E[l2]);
-  const T* const pF1 = uni((const T*)D.F[l1]);
-  const T* const pF2 = uni((const T*)D.F[l2]);
-  const T* const pG1 = uni((const T*)D.G[l1]);
-  const T* const pG2 = uni((const T*)D.G[l2]);
-  const T* const pE3 = CORR ? uni((const T*)D.E[s2]) : nullptr;
-  const T* const pF3 = CORR ? uni((const T*)D.F[s2]) : nullptr;
-  const T* const pG3 = CORR ? uni((const T*)D.G[s2]) : nullptr;
+  const T* const pE1 = uni((const T*)D.E[l1]) + tI;
+  const T* const pE2 = uni((const T*)D.E[l2]) + tI;
+  const T* const pF1 = uni((const T*)D.F[l1]) + tI;
+  const T* const pF2 = uni((const T*)D.F[l2]) + tI;
+  const T* const pG1 = uni((const T*)D.G[l1]) + tI;
+  const T* const pG2 = uni((const T*)D.G[l2]) + tI;
+  const T* const pE3 = CORR ? uni((const T*)D.E[s2]) + tI : nullptr;
+  const T* const pF3 = CORR ? uni((const T*)D.F[s2]) + tI : nullptr;
+  const T* const pG3 = CORR ? uni((const T*)D.G[s2]) + tI : nullptr;
   V2 rw[KW], rp[KW], rq[KW], rc[KC], h1p[KB], h2p[KB], h1q[KB], h2q[KB];
   // keep the load groups in this order (the waits are in issue order)
   __builtin_amdgcn_sched_barrier(0);
   {
     // the state the spatial operator is taken of: level n, or the predicted level
-    const T* w = uni((const T*)(CORR ? D.w[2] : D.w[par]));
-    const T* Pn = uni((const T*)D.P[CORR ? s2 : slot]);
-    const T* Qn = uni((const T*)D.Q[CORR ? s2 : slot]);
-    const unsigned oW = (unsigned)(j0 * pitch + xoff + i0 - 2 + cP);       // radius-2 tile
+    const T* w = uni((const T*)(CORR ? D.w[2] : D.w[par])) + tG;
+    const T* Pn = uni((const T*)D.P[CORR ? s2 : slot]) + tG;
+    const T* Qn = uni((const T*)D.Q[CORR ? s2 : slot]) + tG;
+    const unsigned oW = (unsigned)(jl * pitch + xo + il - 2 + cP);         // radius-2 tile
 #pragma unroll
     for (int k = 0; k < KW; ++k) {
       const unsigned o = oW + (unsigned)(rowW(k) * pitch);
@@ -1440,16 +1452,16 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
       rp[k] = ldv<2>(Pn, o);
       rq[k] = ldv<2>(Qn, o);
     }
-    const T* Dc = uni((const T*)D.Dc);
-    const unsigned oC = (unsigned)(j0 * cpitch + i0 + cC);                 // corners from i0 - 2
+    const T* Dc = uni((const T*)D.Dc) + tC;
+    const unsigned oC = (unsigned)(jl * cpitch + il + cC);                 // corners from i0 - 2
 #pragma unroll
     for (int k = 0; k < KC; ++k) rc[k] = ldv<2>(Dc, oC + (unsigned)(rowC(k) * cpitch));
     // radius-1 rows j0-1 .. j0+TY, in the radius-2 tile's columns
-    const unsigned oB = (unsigned)((j0 + 1) * pitch + xoff + i0 - 2 + cP);
+    const unsigned oB = (unsigned)((jl + 1) * pitch + xo + il - 2 + cP);
     if (CORR) {
       // level n, for the change of the F*, G* terms
-      const T* P1 = uni((const T*)D.P[slot]);
-      const T* Q1 = uni((const T*)D.Q[slot]);
+      const T* P1 = uni((const T*)D.P[slot]) + tG;
+      const T* Q1 = uni((const T*)D.Q[slot]) + tG;
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
         const unsigned o = oB + (unsigned)(rowB(k) * pitch);
@@ -1465,10 +1477,10 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
       // that is loaded anyway (n-1, else the staged level n), so its loads
       // hit the cache instead of reaching HBM.
       const int u1 = sb1 != 0.0 ? s1 : slot, u2 = sb2 != 0.0 ? s2 : u1;
-      const T* P1 = uni((const T*)D.P[u1]);
-      const T* P2 = uni((const T*)D.P[u2]);
-      const T* Q1 = uni((const T*)D.Q[u1]);
-      const T* Q2 = uni((const T*)D.Q[u2]);
+      const T* P1 = uni((const T*)D.P[u1]) + tG;
+      const T* P2 = uni((const T*)D.P[u2]) + tG;
+      const T* Q1 = uni((const T*)D.Q[u1]) + tG;
+      const T* Q2 = uni((const T*)D.Q[u2]) + tG;
 #pragma unroll
       for (int k = 0; k < KB; ++k) {
         const unsigned o = oB + (unsigned)(rowB(k) * pitch);
@@ -1630,8 +1642,8 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
   // ---- phase 2: per-cell right-hand sides and AB3 update -------------------
   const T B = D.B, gn2 = D.gn2, cf = D.cf;
   const T a0 = (T)sa0;
-  T* const wn = uni(CORR ? D.w[par ^ 1] : (D.corrector ? D.w[2] : D.w[par ^ 1]));
-  const T* const wbase = uni((const T*)D.w[par]);   // w^n (the corrector's base)
+  T* const wn = uni(CORR ? D.w[par ^ 1] : (D.corrector ? D.w[2] : D.w[par ^ 1])) + tG;
+  const T* const wbase = uni((const T*)D.w[par]) + tG;   // w^n (the corrector's base)
   // The thread's cells are consecutive columns of one row, and the body is
   // branch-free, so the stencil reads and the eta / depth values they share
   // are formed once for all of them (cells outside the domain compute
@@ -1726,9 +1738,9 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
     sm.x.s.v[o] = in ? a0 * g_ + hG[k] : T(0);
   }
   {
-    T* const E0 = uni(D.E[slot]);
-    T* const F0 = uni(D.F[slot]);
-    T* const G0 = uni(D.G[slot]);
+    T* const E0 = uni(D.E[slot]) + tI;
+    T* const F0 = uni(D.F[slot]) + tI;
+    T* const G0 = uni(D.G[slot]) + tI;
     if (all_in) {
       if (!CORR) {
         stv_nt(E0, oI, ve);
@@ -1817,8 +1829,8 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
   {
     V xp, xq, pb, qb;
     if (CORR) {
-      pb = ldv<CPT>(uni((const T*)D.P[slot]), oG);
-      qb = ldv<CPT>(uni((const T*)D.Q[slot]), oG);
+      pb = ldv<CPT>(uni((const T*)D.P[slot]) + tG, oG);
+      qb = ldv<CPT>(uni((const T*)D.Q[slot]) + tG, oG);
     }
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
@@ -1826,8 +1838,8 @@ __global__ void __launch_bounds__(THREADS) k_rhs(const DomDev<T>* __restrict__ d
       xp.v[k] = (CORR ? pb.v[k] : sm.p[C0]) + sm.x.s.u[vr * TXP + vc + k];
       xq.v[k] = (CORR ? qb.v[k] : sm.q[C0]) + sm.x.s.v[vr * TXP + vc + k];
     }
-    stv_nt(uni(D.xhP), oI, xp);
-    stv_nt(uni(D.xhQ), oI, xq);
+    stv_nt(uni(D.xhP) + tI, oI, xp);
+    stv_nt(uni(D.xhQ) + tI, oI, xq);
   }
 }
 
@@ -2122,7 +2134,7 @@ struct alignas(16) FinSmem {
 // corrector.  MODE 1: the same where some do; for those it finalizes the
 // predicted level (surface in w[2], no sponge, no run-up record).  MODE 2:
 // finalizes the corrector of the domains that run it.
-template <typename T, int TY, int MX, int MODE, int THREADS = NT>
+template <typename T, int TY, int MX, int MODE, int THREADS = NT, bool BIG = false>
 __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__ doms, const int* __restrict__ tile_map,
                                              int nd, int swizzle) {
   using S = FinSmem<T, TY, MX>;
@@ -2152,8 +2164,13 @@ __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__
   // cells of a thread: row vr, columns vc .. vc+CPT-1 (as in the stencil kernel)
   int vr, vc;
   cell_of<T, CPT>(tid, vr, vc);
-  const unsigned oI = (unsigned)((j0 + vr) * ipitch + i0 + vc);
-  const unsigned oG = (unsigned)((j0 + vr + 2) * pitch + xoff + i0 + vc);
+  // where the lanes count from, as in the stencil kernel
+  const int jl = BIG ? 0 : j0, il = BIG ? 0 : i0, xo = BIG ? 0 : xoff;
+  const size_t tI = BIG ? (size_t)j0 * ipitch + i0 : 0;
+  const size_t tG = BIG ? (size_t)j0 * pitch + xoff + i0 : 0;
+  const size_t tC = BIG ? (size_t)j0 * cpitch + i0 : 0;
+  const unsigned oI = (unsigned)((jl + vr) * ipitch + il + vc);
+  const unsigned oG = (unsigned)((jl + vr + 2) * pitch + xo + il + vc);
   // All loads first, in the order they are needed (the waits are in issue
   // order): the corners of the tile's cells and their neighbours (pairs of
   // corners, rows read in groups, no clamping: the fields are padded to
@@ -2168,8 +2185,8 @@ __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__
   V2 rc[KC];
   __builtin_amdgcn_sched_barrier(0);
   {
-    const T* Dc = uni((const T*)D.Dc);
-    const unsigned oC = (unsigned)((j0 + 1) * cpitch + i0 + cC);   // corner (i0-2+cC, j0-1)
+    const T* Dc = uni((const T*)D.Dc) + tC;
+    const unsigned oC = (unsigned)((jl + 1) * cpitch + il + cC);   // corner (i0-2+cC, j0-1)
 #pragma unroll
     for (int k = 0; k < KC; ++k) rc[k] = ldv<2>(Dc, oC + (unsigned)(rowC(k) * cpitch));
   }
@@ -2199,9 +2216,9 @@ __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__
     xr = xsol ? xrx : xry;
   }
   __builtin_amdgcn_sched_barrier(0);
-  const V lp = ldv_nt<CPT>(uni((const T*)D.xhP), oI);
-  const V lq = ldv_nt<CPT>(uni((const T*)D.xhQ), oI);
-  const V lw = ldv_nt<CPT>((const T*)w, oG);
+  const V lp = ldv_nt<CPT>(uni((const T*)D.xhP) + tI, oI);
+  const V lq = ldv_nt<CPT>(uni((const T*)D.xhQ) + tI, oI);
+  const V lw = ldv_nt<CPT>((const T*)w + tG, oG);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int k = 0; k < KC; ++k) {
@@ -2302,14 +2319,14 @@ __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__
         qv *= fac;
         vp.v[k] = p;
         vq.v[k] = qv;
-        stu(w, oG + k, wv);
+        stu(w + tG, oG + k, wv);
       }
     }
     const T h = fmax(wv + Db, T(0));
     if (D.runup && !pred && h > D.runup_delta) {
       // run-up record: highest surface over the inundated states (NaN until
       // the first one)
-      const gp<T> wm = gbl(D.wmax);
+      const gp<T> wm = gbl(D.wmax) + tI;
       const unsigned oi = oI + (unsigned)k;
       if (!(wm[oi] >= wv)) wm[oi] = wv;
     }
@@ -2323,14 +2340,14 @@ __global__ void __launch_bounds__(THREADS) k_final(const DomDev<T>* __restrict__
     if (i < 2 || i >= nx - 2 || j < 2 || j >= ny - 2) ghost_cell(D, w, P, Q, i, j, wv, p, qv, st->gw, st->gP);
   }
   if (all_in) {
-    stv_nt(P, oG, vp);
-    stv_nt(Q, oG, vq);
+    stv_nt(P + tG, oG, vp);
+    stv_nt(Q + tG, oG, vq);
   } else if (row_in) {
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       if (i0 + vc + k >= nx) break;
-      stu(P, oG + k, vp.v[k]);
-      stu(Q, oG + k, vq.v[k]);
+      stu(P + tG, oG + k, vp.v[k]);
+      stu(Q + tG, oG + k, vq.v[k]);
     }
   }
   // block max -> one word per tile (max commutes with the widening to FP64,

@@ -524,6 +524,7 @@ struct Launch {
   int tiles_all = 0;            // tiles of all launches that run side by side (the lanes of a batch)
   int ty = 0, mx = 0;           // tile shape shared by the members
   int any_pc = 0;               // some member runs the corrector pass
+  int big = 0;                  // a field exceeds 4 GiB (single domains: the work map of a batch has no room for its tiles)
   int swizzle = 1;              // XCD-aware tile order (schedule, set per batch)
   hipGraphExec_t graph = nullptr;
   int graph_steps = 0;          // steps per replay (0 = none)
@@ -876,6 +877,7 @@ static int create_t(bq_domain* d, const double* depth_c) {
   d->L.tile_map = d->L.line_map = nullptr;
   d->L.nd = 1;
   d->L.any_pc = D.corrector;
+  d->L.big = max_field_elements<T>(p) * sizeof(T) > ((size_t)1 << 32);
   d->L.tiles = d->L.tiles_all = D.tiles_x * D.tiles_y;
   d->L.lblocks = line_blocks(p->nx, p->ny);
   d->L.ty = sh0.ty;
@@ -1020,6 +1022,11 @@ static void threads_dispatch(int n, F&& f) {
   f(IC<NT>{});
 }
 
+// a domain with fields over 4 GiB keeps the shape it was created with (only
+// batches change shapes) and fills the chip with blocks of any width
+template <typename T, int TY, int MX>
+constexpr bool big_shape = TY == Cfg<T>::shape(0).ty && MX == Cfg<T>::shape(0).mx;
+
 // the stencil/update kernel (pass 0: AB3 step, 1: corrector) and the
 // finalize kernel (mode as in k_final) in the launch's tile shape
 template <typename T>
@@ -1027,6 +1034,13 @@ static void launch_rhs(const Launch& L, hipStream_t s, int pass) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
+    if constexpr (big_shape<T, TY, MX>) {
+      if (L.big) {
+        if (pass == 0) k_rhs<T, TY, MX, false, NT, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        else k_rhs<T, TY, MX, true, NT, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        return;
+      }
+    }
     threads_dispatch<TX * TY>(rhs_threads(L.tiles_all, TX * TY, sizeof(T)), [&](auto threads) {
       constexpr int N = decltype(threads)::value;
       if constexpr (N <= 512) {
@@ -1042,6 +1056,14 @@ static void launch_final(const Launch& L, hipStream_t s, int mode) {
   shape_dispatch<T>(L.ty, L.mx, [&](auto tyc, auto mxc) {
     constexpr int TY = decltype(tyc)::value, MX = decltype(mxc)::value;
     const DomDev<T>* tab = (const DomDev<T>*)L.table;
+    if constexpr (big_shape<T, TY, MX>) {
+      if (L.big) {
+        if (mode == 0) k_final<T, TY, MX, 0, NT, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        else if (mode == 1) k_final<T, TY, MX, 1, NT, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        else k_final<T, TY, MX, 2, NT, true><<<L.tiles, NT, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
+        return;
+      }
+    }
     threads_dispatch<TX * TY>(final_threads(L.tiles_all, TX * TY, sizeof(T)), [&](auto threads) {
       constexpr int N = decltype(threads)::value;
       if (mode == 0) k_final<T, TY, MX, 0, N><<<L.tiles, N, 0, s>>>(tab, L.tile_map, L.nd, L.swizzle);
