@@ -232,10 +232,9 @@ __device__ __forceinline__ void stv_nt(T* base, unsigned off, const Vec<T, N>& v
 }
 
 // Square root, reciprocal and x^(-1/3) for any argument.  FP64: the library's
-// correctly rounded root and division, and an inverse cube root good to 1.2
-// units in the last place; FP32: the hardware's transcendental instructions
-// (about 1 ulp), whose error is far below the FP32 path's own rounding of the
-// state.
+// correctly rounded root and division, and an inverse cube root good to 1.43 x
+// 2^-53; FP32: the hardware's transcendental instructions (about 1 ulp), whose
+// error is far below the FP32 path's own rounding of the state.
 template <typename T> __device__ __forceinline__ T fsqrt(T x);
 template <typename T> __device__ __forceinline__ T frcp(T x);
 template <typename T> __device__ __forceinline__ T frcbrt(T x);   // x^(-1/3), x > 0
